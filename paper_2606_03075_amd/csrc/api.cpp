@@ -117,6 +117,7 @@ struct ScoreWs {
     float* colsum;
     float* vmh;
     float* part;
+    float* stat;
     size_t bytes;
 };
 
@@ -133,6 +134,10 @@ ScoreWs score_workspace(const Shape& s, const RowPlan& rp, void* base) {
     off = align_up(off + sizeof(float) * bl * s.H);
     w.part = reinterpret_cast<float*>(b ? b + off : nullptr);
     off = align_up(off + sizeof(float) * bl * s.Hkv * (size_t)std::max(rp.rowgroups, 1) * s.Nv);
+    // a split statistics sweep: [3][splits][B*L*H][N_q] partial row statistics
+    const int ss = tgvkv::stats_splits(s, rp);
+    w.stat = reinterpret_cast<float*>(b && ss > 1 ? b + off : nullptr);
+    if (ss > 1) off = align_up(off + sizeof(float) * 3 * (size_t)ss * bl * s.H * s.Nq);
     w.bytes = off;
     return w;
 }
@@ -234,7 +239,7 @@ tgvkv_status tgvkv_score(const tgvkv_problem* problem, const tgvkv_opts* opts, i
 
     hipError_t e = hipSuccess;
     if (lse_in) {
-        e = tgvkv::launch_score_text(s, q, kk, lse, w.vm, w.colsum, w.vmh, true, stream);
+        e = tgvkv::launch_score_text(s, rp, q, kk, lse, w.vm, w.colsum, w.vmh, nullptr, true, stream);
         if (e == hipSuccess) e = tgvkv::launch_score_fin(s, w.colsum, w.vmh, s_txt, w_txt, tv_mass, false, stream);
         if (e == hipSuccess)
             e = tgvkv::launch_score_vision(s, rp, q, kk, lse, w_txt, nullptr, vthr, w.part, w.vm, stream);
@@ -247,9 +252,9 @@ tgvkv_status tgvkv_score(const tgvkv_problem* problem, const tgvkv_opts* opts, i
         e = tgvkv::launch_score_stats_text(s, rp, q, kk, lse, w.vm, w.colsum, w.vmh, stream);
         if (e == hipSuccess) e = tgvkv::launch_score_fin(s, w.colsum, w.vmh, s_txt, w_txt, tv_mass, true, stream);
     } else {
-        if (phases & TGVKV_SCORE_STATS) e = tgvkv::launch_score_stats(s, rp, q, kk, lse, w.vm, stream);
+        if (phases & TGVKV_SCORE_STATS) e = tgvkv::launch_score_stats(s, rp, q, kk, lse, w.vm, w.stat, !both, stream);
         if ((phases & TGVKV_SCORE_TEXT) && e == hipSuccess) {
-            e = tgvkv::launch_score_text(s, q, kk, lse, w.vm, w.colsum, w.vmh, false, stream);
+            e = tgvkv::launch_score_text(s, rp, q, kk, lse, w.vm, w.colsum, w.vmh, both ? w.stat : nullptr, false, stream);
             if (e == hipSuccess) e = tgvkv::launch_score_fin(s, w.colsum, w.vmh, s_txt, w_txt, tv_mass, true, stream);
         }
     }

@@ -12,7 +12,9 @@
 //   score_stats_text  sweep 1 followed by the unit's text pass in the same
 //                 workgroup, when one workgroup holds all of a unit's question rows;
 //   score_text    text rows x text keys: system-row normalisers, then the
-//                 text->text probabilities' column sums per head (Eq. (9));
+//                 text->text probabilities' column sums per head (Eq. (9)); with few units
+//                 sweep 1 is split over the keys, and this merges the shares' statistics
+//                 (score_stats_merge does when the statistics are asked for alone);
 //   score_fin     head means -> s^T, w, w~ (Eq. (7), (9)) and the layer's
 //                 text->vision mass (Eq. (5)-(6));
 //   score_vision  sweep 2: question rows x vision keys, p = exp(z - lse),
@@ -38,17 +40,39 @@ namespace {
 
 using namespace core;
 
+// Partial row statistics of a sweep whose keys are split over nsplit workgroups: [3][nsplit][rows]
+// (reference max in base-2 units, sum, vision sum), rows = B*L*H*N_q.  merge_row adds a row's
+// shares in share order and gives its normaliser (natural log) and vision mass.
+__device__ __forceinline__ void merge_row(const float* __restrict__ ws_stat, size_t rows, int nsplit, size_t r,
+                                          float& ln, float& vm) {
+    const size_t plane = rows * nsplit;
+    float m = ws_stat[r], l = ws_stat[plane + r], v = ws_stat[2 * plane + r];
+#pragma unroll 4
+    for (int sp = 1; sp < nsplit; ++sp) {
+        const size_t x = sp * rows + r;
+        merge_stats(m, l, v, ws_stat[x], ws_stat[plane + x], ws_stat[2 * plane + x]);
+    }
+    ln = (m + log2f(l)) * kLn2;
+    vm = v / l;
+}
+
+// Sweep 1 of one share of a unit's keys, for one row group.  With few units one workgroup per
+// unit leaves most of the chip idle, so the keys are split over nsplit workgroups (stats_splits);
+// the shares' statistics are merged by the text pass or by score_stats_merge.
 template <int D, int NSLOT, int KS>
-__global__ __launch_bounds__(kThreads) void score_stats_kernel(Shape s, int rowgroups,
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(NSLOT >= 6 ? 2 : 1))) void score_stats_kernel(Shape s, int rowgroups,
                                                                const uint16_t* __restrict__ q_text,
                                                                const uint16_t* __restrict__ k,
                                                                float* __restrict__ lse,
-                                                               float* __restrict__ ws_vm) {
+                                                               float* __restrict__ ws_vm, int nsplit,
+                                                               float* __restrict__ ws_stat) {
     constexpr int RSETS = 4 / KS;
     __shared__ __attribute__((aligned(16))) char tiles[2][Geo<D>::TILE_BYTES];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int rs = wave % RSETS, kp = wave / RSETS;
     int bid = blockIdx.x;
+    const int sp = bid % nsplit;
+    bid /= nsplit;
     const int rg = bid % rowgroups;
     bid /= rowgroups;
     const int kvh = bid % s.Hkv;
@@ -62,19 +86,43 @@ __global__ __launch_bounds__(kThreads) void score_stats_kernel(Shape s, int rowg
     load_qrows<D, NSLOT, KS>(s, q_text, bl, kvh, rb0, qf, qrow);
     float m[NSLOT], lsum[NSLOT], vsum[NSLOT];
     const uint16_t* kbase = k + ((size_t)bl * s.Hkv + kvh) * (size_t)s.N * D;
-    stats_sweep<D, NSLOT, KS>(s, kbase, 0, s.N, qf, qrow, tiles, m, lsum, vsum);
+    const int per = ((s.N + kTile - 1) / kTile + nsplit - 1) / nsplit * kTile;  // keys per share
+    const int kbeg = min(sp * per, s.N), kend = min(kbeg + per, s.N);
+    stats_sweep<D, NSLOT, KS>(s, kbase, kbeg, kend, qf, qrow, tiles, m, lsum, vsum);
     if (kp == 0 && lane < 16) {
+        const size_t rows = (size_t)s.B * s.L * s.H * s.Nq;
 #pragma unroll
         for (int sl = 0; sl < NSLOT; ++sl) {
             const int rb = slot_block<RSETS>(rb0, rs, sl);
             const int qi = qrow[sl];
             if (rb < NB && qi < s.Nq) {
                 const size_t head = (size_t)bl * s.H + kvh * s.G + rb / QB;
-                lse[head * s.Nt + s.Ns + qi] = (m[sl] + log2f(lsum[sl])) * kLn2;
-                ws_vm[head * s.Nq + qi] = vsum[sl] / lsum[sl];
+                if (nsplit > 1) {
+                    float* w = ws_stat + sp * rows + head * s.Nq + qi;
+                    w[0] = m[sl];
+                    w[rows * nsplit] = lsum[sl];
+                    w[2 * rows * nsplit] = vsum[sl];
+                } else {
+                    lse[head * s.Nt + s.Ns + qi] = (m[sl] + log2f(lsum[sl])) * kLn2;
+                    ws_vm[head * s.Nq + qi] = vsum[sl] / lsum[sl];
+                }
             }
         }
     }
+}
+
+// Normalisers and vision masses from the shares' statistics, one thread per question row (for
+// calls that ask for the statistics alone; the text pass merges them itself).
+__global__ __launch_bounds__(kThreads) void score_stats_merge_kernel(Shape s, const float* __restrict__ ws_stat,
+                                                                     int nsplit, float* __restrict__ lse,
+                                                                     float* __restrict__ ws_vm) {
+    const size_t rows = (size_t)s.B * s.L * s.H * s.Nq;
+    const size_t r = (size_t)blockIdx.x * kThreads + threadIdx.x;
+    if (r >= rows) return;
+    float ln, vm;
+    merge_row(ws_stat, rows, nsplit, r, ln, vm);
+    lse[r / s.Nq * s.Nt + s.Ns + r % s.Nq] = ln;
+    ws_vm[r] = vm;
 }
 
 // Sweep 1 and the text pass of one unit in one workgroup, for shapes where one
@@ -156,50 +204,67 @@ score_stats_text_kernel(Shape s, const uint16_t* __restrict__ q_text, const uint
     if (text_mode == 1) {
         // the unit's text keys go into the freed tiles after the normalisers and masses
         const size_t off = ((size_t)s.G * (s.Nt + s.Nq) * sizeof(float) + 15) & ~(size_t)15;
-        text_pass_lds<D>(s, bl, kvh, q_text, k, lse, lse2s, &tiles[0][0] + off,
+        text_pass_lds<D>(s, bl, kvh, 0, s.G, q_text, k, lse, lse2s, &tiles[0][0] + off,
                          2LL * Geo<D>::TILE_BYTES - (long long)off, ws_colsum);
     } else {
-        text_pass<D>(s, bl, kvh, q_text, k, lse, lse2s, ws_colsum);
+        text_pass<D>(s, bl, kvh, 0, s.G, q_text, k, lse, lse2s, ws_colsum);
     }
 }
 
+// The text pass of one unit, or with hsplit > 1 of one of its query heads (hsplit = G).
+// ws_stat non-null: the question rows' statistics come as nsplit shares, merged here.
 template <int D>
 __global__ __launch_bounds__(kThreads) void score_text_kernel(Shape s, const uint16_t* __restrict__ q_text,
                                                               const uint16_t* __restrict__ k,
                                                               float* __restrict__ lse,
-                                                              const float* __restrict__ ws_vm,
+                                                              float* __restrict__ ws_vm,
                                                               float* __restrict__ ws_colsum,
-                                                              float* __restrict__ ws_vmh, int lse_given,
-                                                              long long kl_bytes) {
+                                                              float* __restrict__ ws_vmh, int lse_given, int hsplit,
+                                                              long long kl_bytes, const float* __restrict__ ws_stat,
+                                                              int nsplit) {
     // [G][N_t] row normalisers, base-2 units; with kl_bytes > 0, then the staged text pass's
     // LDS (text_pass_lds), 16-byte aligned
     extern __shared__ float lse2s[];
     const int tid = threadIdx.x;
-    const int kvh = blockIdx.x % s.Hkv;
-    const int bl = blockIdx.x / s.Hkv;
-    const size_t head0 = (size_t)bl * s.H + kvh * s.G;
+    const int G = s.G / hsplit;  // query heads of this workgroup: g0 .. g0 + G - 1
+    const int g0 = (blockIdx.x % hsplit) * G;
+    const int kvh = blockIdx.x / hsplit % s.Hkv;
+    const int bl = blockIdx.x / hsplit / s.Hkv;
+    const size_t head0 = (size_t)bl * s.H + kvh * s.G + g0;
     if (lse_given) {
         // every text row's normaliser comes from the caller (a prefill kernel's row log-sum-exp)
-        for (int x = tid; x < s.G * s.Nt; x += kThreads) lse2s[x] = lse[head0 * s.Nt + x] * kLog2e;
-        if (kl_bytes > 0) {
-            __syncthreads();
-            char* kl = reinterpret_cast<char*>(lse2s) + ((size_t)s.G * s.Nt * sizeof(float) + 15) / 16 * 16;
-            text_pass_lds<D>(s, bl, kvh, q_text, k, lse, lse2s, kl, kl_bytes, ws_colsum, true);
-            return;
-        }
+        for (int x = tid; x < G * s.Nt; x += kThreads) lse2s[x] = lse[head0 * s.Nt + x] * kLog2e;
     } else {
-        for (int x = tid; x < s.G * s.Nq; x += kThreads) {
+        for (int x = tid; x < G * s.Nq; x += kThreads) {
             const int g = x / s.Nq, qi = x % s.Nq;
-            lse2s[g * s.Nt + s.Ns + qi] = lse[(head0 + g) * s.Nt + s.Ns + qi] * kLog2e;
+            float ln;
+            if (ws_stat != nullptr) {
+                float vm;
+                merge_row(ws_stat, (size_t)s.B * s.L * s.H * s.Nq, nsplit, (head0 + g) * s.Nq + qi, ln, vm);
+                lse[(head0 + g) * s.Nt + s.Ns + qi] = ln;
+                ws_vm[(head0 + g) * s.Nq + qi] = vm;
+            } else {
+                ln = lse[(head0 + g) * s.Nt + s.Ns + qi];
+            }
+            lse2s[g * s.Nt + s.Ns + qi] = ln * kLog2e;
         }
-        if (tid < s.G) {
+        __syncthreads();
+        // per query head: the sum of its question rows' vision masses (one wave per head)
+        for (int g = tid >> 6; g < G; g += kThreads / 64) {
             float a = 0.f;
-            for (int qi = 0; qi < s.Nq; ++qi) a += ws_vm[(head0 + tid) * s.Nq + qi];
-            ws_vmh[head0 + tid] = a;
+            for (int qi = tid & 63; qi < s.Nq; qi += 64) a += ws_vm[(head0 + g) * s.Nq + qi];
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) a += shfl_xor(a, off);
+            if ((tid & 63) == 0) ws_vmh[head0 + g] = a;
         }
     }
     __syncthreads();
-    text_pass<D>(s, bl, kvh, q_text, k, lse, lse2s, ws_colsum, lse_given != 0);
+    if (kl_bytes > 0) {
+        char* kl = reinterpret_cast<char*>(lse2s) + ((size_t)G * s.Nt * sizeof(float) + 15) / 16 * 16;
+        text_pass_lds<D>(s, bl, kvh, g0, G, q_text, k, lse, lse2s, kl, kl_bytes, ws_colsum, lse_given != 0);
+    } else {
+        text_pass<D>(s, bl, kvh, g0, G, q_text, k, lse, lse2s, ws_colsum, lse_given != 0);
+    }
 }
 
 // One wave per (unit, query head, 16-key block) of the text->text column sums, when
@@ -453,6 +518,10 @@ int resident_workgroups(const void* kernel, size_t dyn_lds) {
 
 }  // namespace
 
+// Units (KV heads of all sequences and layers) up to which the text pass runs one workgroup per
+// query head.
+constexpr long long kHeadSplitUnits = 512;
+
 RowPlan plan_question_rows(const Shape& s) {
     const int QB = (s.Nq + 15) / 16;
     const int NB = s.G * QB;
@@ -469,20 +538,49 @@ RowPlan plan_question_rows(const Shape& s) {
     return rp;
 }
 
+// Shares of a unit's keys that the statistics sweep is split over.  One workgroup per (unit, row
+// group) leaves the chip idle when there are few of them; the split fills one round of resident
+// workgroups (4, 3, 2, 2 per CU at 1, 2, 4, 6 row slots), each share at least kMinShareTiles key
+// tiles.  It costs the separate text pass, so it is only taken from 12 key tiles on, or from 6 when
+// four or more row slots make each tile long.  Statistics and text, one layer: 32 units of 64
+// question rows, 447 keys 15.5 us whole against 17.0 split, 699 keys 21.0 against 18.5, 2979 keys
+// about 50 against 21; 16 units of 336 rows, 464 keys 41.7 against 28.3.  112 units of 336 rows
+// over 8256 keys: 288 us whole, 124 split.  Shares of 3 tiles against 4: 17.3 against 20.9 us in
+// the sweep at 4 units, 1-2 us shorter at 32.
+constexpr int kMinShareTiles = 3;
+constexpr int kMaxShares = 32;
+
+int stats_splits(const Shape& s, const RowPlan& rp) {
+    const long long units = (long long)s.B * s.L * s.Hkv * rp.rowgroups;
+    const int tiles = (s.N + kTile - 1) / kTile;
+    if (units <= 0 || tiles < (rp.nslot >= 4 ? 6 : 12)) return 1;
+    const int per_cu = rp.nslot == 1 ? 4 : rp.nslot == 2 ? 3 : 2;
+    const int n = (int)std::min<long long>(std::min<long long>(256 * per_cu / units, tiles / kMinShareTiles), kMaxShares);
+    if (n <= 1) return 1;
+    const int per = (tiles + n - 1) / n;  // tiles per share; no share is empty
+    return (tiles + per - 1) / per;
+}
+
 hipError_t launch_score_stats(const Shape& s, const RowPlan& rp, const uint16_t* q_text, const uint16_t* k,
-                              float* lse, float* ws_vm, hipStream_t st) {
-    const long long nblk = (long long)s.B * s.L * s.Hkv * rp.rowgroups;
+                              float* lse, float* ws_vm, float* ws_stat, bool merge, hipStream_t st) {
+    const int nsplit = stats_splits(s, rp);
+    const long long nblk = (long long)s.B * s.L * s.Hkv * rp.rowgroups * nsplit;
     if (nblk == 0) return hipSuccess;
     dim3 grid((unsigned)nblk), block(kThreads);
     if (s.D == 128)
-        TGVKV_ROWPLAN_DISPATCH(score_stats_kernel, 128, rp, grid, block, 0, st, s, rp.rowgroups, q_text, k, lse, ws_vm);
+        TGVKV_ROWPLAN_DISPATCH(score_stats_kernel, 128, rp, grid, block, 0, st, s, rp.rowgroups, q_text, k, lse, ws_vm, nsplit, ws_stat);
     else
-        TGVKV_ROWPLAN_DISPATCH(score_stats_kernel, 64, rp, grid, block, 0, st, s, rp.rowgroups, q_text, k, lse, ws_vm);
+        TGVKV_ROWPLAN_DISPATCH(score_stats_kernel, 64, rp, grid, block, 0, st, s, rp.rowgroups, q_text, k, lse, ws_vm, nsplit, ws_stat);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess || nsplit == 1 || !merge) return e;
+    const long long rows = (long long)s.B * s.L * s.H * s.Nq;
+    hipLaunchKernelGGL(score_stats_merge_kernel, dim3((unsigned)((rows + kThreads - 1) / kThreads)), block, 0, st, s,
+                       ws_stat, nsplit, lse, ws_vm);
     return hipGetLastError();
 }
 
 bool stats_text_eligible(const Shape& s, const RowPlan& rp) {
-    if (rp.rowgroups != 1 || s.Nt == 0) return false;
+    if (rp.rowgroups != 1 || s.Nt == 0 || stats_splits(s, rp) > 1) return false;
     const long long floats = (long long)s.G * (s.Nt + s.Nq);
     const long long tile_bytes = 2LL * kTile * (2 * s.D + 16);
     return floats * 4 <= tile_bytes;
@@ -517,33 +615,27 @@ hipError_t launch_score_stats_text(const Shape& s, const RowPlan& rp, const uint
     return hipGetLastError();
 }
 
-hipError_t launch_score_text(const Shape& s, const uint16_t* q_text, const uint16_t* k, float* lse,
-                             const float* ws_vm, float* ws_colsum, float* ws_vmh, bool lse_given, hipStream_t st) {
+hipError_t launch_score_text(const Shape& s, const RowPlan& rp, const uint16_t* q_text, const uint16_t* k, float* lse,
+                             float* ws_vm, float* ws_colsum, float* ws_vmh, const float* ws_stat, bool lse_given,
+                             hipStream_t st) {
     const long long nblk = (long long)s.B * s.L * s.Hkv;
     if (nblk == 0 || s.Nt == 0) return hipSuccess;
-    if (lse_given) {
-        // the unit's text keys staged in LDS by one workgroup per unit (text_pass_lds; in
-        // chunks of key blocks when they do not all fit beside the normalisers within 64 KB):
-        // against one wave per (unit, head, 16-key block) walking the row blocks from global
-        // memory, at llavanext 80 -> 20 us
-        const int TB = (s.Nt + 15) / 16;
-        const long long head = ((long long)s.G * s.Nt * 4 + 15) / 16 * 16;
-        const long long kl = std::min<long long>(
-            (s.D == 128 ? text_part_bytes<128>(s.G, s.Nt) : text_part_bytes<64>(s.G, s.Nt)) +
-                16LL * TB * (2 * s.D + 16),
-            65536 - head);
-        const bool fits = s.D == 128 ? text_lds_fits<128>(s.G, 0, s.Nt, kl) : text_lds_fits<64>(s.G, 0, s.Nt, kl);
-        if (s.Nt > 0 && kl > 0 && fits) {
-            const size_t lds = (size_t)(head + kl);
-            if (s.D == 128)
-                hipLaunchKernelGGL(score_text_kernel<128>, dim3((unsigned)nblk), dim3(kThreads), lds, st, s, q_text,
-                                   k, lse, ws_vm, ws_colsum, ws_vmh, 1, kl);
-            else
-                hipLaunchKernelGGL(score_text_kernel<64>, dim3((unsigned)nblk), dim3(kThreads), lds, st, s, q_text,
-                                   k, lse, ws_vm, ws_colsum, ws_vmh, 1, kl);
-            return hipGetLastError();
-        }
-        const long long items = nblk * s.G * ((s.Nt + 15) / 16);
+    // with few units, one workgroup per query head: each stages the unit's text keys again (from
+    // cache), but a unit's heads no longer follow one another in the same four waves
+    const int hsplit = s.G > 1 && nblk <= kHeadSplitUnits ? s.G : 1;
+    const int G = s.G / hsplit;
+    // the unit's text keys staged in LDS (text_pass_lds; in chunks of key blocks when they do not
+    // all fit beside the normalisers within 64 KB): against one wave per (unit, head, 16-key block)
+    // walking the row blocks from global memory, at llavanext 80 -> 20 us
+    const int TB = (s.Nt + 15) / 16;
+    const long long head = ((long long)G * s.Nt * 4 + 15) / 16 * 16;
+    const long long kl = std::min<long long>(
+        (s.D == 128 ? text_part_bytes<128>(G, s.Nt) : text_part_bytes<64>(G, s.Nt)) + 16LL * TB * (2 * s.D + 16),
+        65536 - head);
+    const int sys = lse_given ? 0 : s.Ns;
+    const bool staged = kl > 0 && (s.D == 128 ? text_lds_fits<128>(G, sys, s.Nt, kl) : text_lds_fits<64>(G, sys, s.Nt, kl));
+    if (lse_given && !staged) {
+        const long long items = nblk * s.G * TB;
         if (s.D == 128)
             hipLaunchKernelGGL(score_text_cols_kernel<128>, dim3((unsigned)items), dim3(64), 0, st, s, q_text, k, lse,
                                ws_colsum);
@@ -552,14 +644,15 @@ hipError_t launch_score_text(const Shape& s, const uint16_t* q_text, const uint1
                                ws_colsum);
         return hipGetLastError();
     }
-    dim3 grid((unsigned)nblk), block(kThreads);
-    const size_t lds = sizeof(float) * (size_t)s.G * s.Nt;
+    dim3 grid((unsigned)(nblk * hsplit)), block(kThreads);
+    const size_t lds = staged ? (size_t)(head + kl) : sizeof(float) * (size_t)G * s.Nt;
+    const int nsplit = ws_stat != nullptr ? stats_splits(s, rp) : 1;
     if (s.D == 128)
         hipLaunchKernelGGL(score_text_kernel<128>, grid, block, lds, st, s, q_text, k, lse, ws_vm, ws_colsum, ws_vmh,
-                           (int)lse_given, 0LL);
+                           (int)lse_given, hsplit, staged ? kl : 0LL, ws_stat, nsplit);
     else
         hipLaunchKernelGGL(score_text_kernel<64>, grid, block, lds, st, s, q_text, k, lse, ws_vm, ws_colsum, ws_vmh,
-                           (int)lse_given, 0LL);
+                           (int)lse_given, hsplit, staged ? kl : 0LL, ws_stat, nsplit);
     return hipGetLastError();
 }
 

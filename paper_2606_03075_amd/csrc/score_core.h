@@ -539,8 +539,8 @@ __device__ void vision_sweep(const Shape& s, const uint16_t* kvis, int vbeg, int
     }
 }
 
-// Text x text pass of one unit.  lse2s [G][N_t] (LDS, base-2 units) must hold the
-// question rows' normalisers.  Computes the system rows' normalisers (system
+// Text x text pass of query heads g0 .. g0 + G - 1 of one unit.  lse2s [G][N_t] (LDS, base-2
+// units) must hold the question rows' normalisers.  Computes the system rows' normalisers (system
 // rows see only system keys, causally) into lse2s and lse, then the column sums
 // of the text->text probabilities per query head into ws_colsum [.., N_t].
 // The work is small and latency-bound: each wave walks its items with the next
@@ -549,12 +549,12 @@ __device__ void vision_sweep(const Shape& s, const uint16_t* kvis, int vbeg, int
 // With lse_given every text row's normaliser is already in lse2s (taken from the
 // caller), the system rows are not recomputed and lse is not written.
 template <int D>
-__device__ void text_pass(const Shape& s, int bl, int kvh, const uint16_t* __restrict__ q_text,
+__device__ void text_pass(const Shape& s, int bl, int kvh, int g0, int G, const uint16_t* __restrict__ q_text,
                           const uint16_t* __restrict__ k, float* __restrict__ lse, float* lse2s,
                           float* __restrict__ ws_colsum, bool lse_given = false) {
     using GG = Geo<D>;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const size_t head0 = (size_t)bl * s.H + kvh * s.G;
+    const size_t head0 = (size_t)bl * s.H + kvh * s.G + g0;
     const uint16_t* kbase = k + ((size_t)bl * s.Hkv + kvh) * (size_t)s.N * D;
     const int koff = (lane >> 4) * 8;
     auto load_frag = [&](bf16x8 (&f)[GG::KSTEPS], const uint16_t* row) {
@@ -564,7 +564,7 @@ __device__ void text_pass(const Shape& s, int bl, int kvh, const uint16_t* __res
 
     // system rows x system keys: row normalisers (C[key][row]: a lane owns row i)
     const int SB = lse_given ? 0 : (s.Ns + 15) >> 4;
-    for (int item = wave; item < s.G * SB; item += 4) {
+    for (int item = wave; item < G * SB; item += 4) {
         const int g = item / SB, rb = item % SB;
         const int i = rb * 16 + (lane & 15);
         const bool rv = i < s.Ns;
@@ -615,7 +615,7 @@ __device__ void text_pass(const Shape& s, int bl, int kvh, const uint16_t* __res
 
     // all text rows x text keys: column sums (C[row][key]: a lane owns key j)
     const int TB = (s.Nt + 15) >> 4;
-    for (int item = wave; item < s.G * TB; item += 4) {
+    for (int item = wave; item < G * TB; item += 4) {
         const int g = item / TB, kb = item % TB;
         const int j = kb * 16 + (lane & 15);
         const int jc = min(j, s.Nt - 1);
@@ -666,7 +666,7 @@ __host__ __device__ constexpr bool text_lds_fits(int G, int Ns, int Nt, long lon
            text_chunk_blocks<D>(G, Nt, kl_bytes) >= ((Ns + 15) / 16 > 1 ? (Ns + 15) / 16 : 1);
 }
 
-// The text pass of text_pass with the unit's text keys staged in LDS (one round of
+// The text pass of text_pass (heads g0 .. g0 + G - 1) with the unit's text keys staged in LDS (one round of
 // loads by the whole workgroup per chunk of key blocks).  Each wave owns 16-row blocks
 // of text rows: it fetches a block's query fragments from global memory (the next
 // item's while the current one is used) and reads every key block it needs from LDS,
@@ -681,18 +681,18 @@ __host__ __device__ constexpr bool text_lds_fits(int G, int Ns, int Nt, long lon
 // system rows' are not computed and lse is not written); kl points at kl_bytes of 16-byte
 // aligned LDS with text_lds_fits<D>(G, N_s, N_t, kl_bytes).
 template <int D>
-__device__ void text_pass_lds(const Shape& s, int bl, int kvh, const uint16_t* __restrict__ q_text,
+__device__ void text_pass_lds(const Shape& s, int bl, int kvh, int g0, int G, const uint16_t* __restrict__ q_text,
                               const uint16_t* __restrict__ k, float* __restrict__ lse, float* lse2s, char* kl,
                               long long kl_bytes, float* __restrict__ ws_colsum, bool lse_given = false) {
     using GG = Geo<D>;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const size_t head0 = (size_t)bl * s.H + kvh * s.G;
+    const size_t head0 = (size_t)bl * s.H + kvh * s.G + g0;
     const uint16_t* kbase = k + ((size_t)bl * s.Hkv + kvh) * (size_t)s.N * D;
     const int TB = (s.Nt + 15) >> 4;
     const int TK = TB * 16;                                       // key rows (the last block padded)
     float* part = reinterpret_cast<float*>(kl);                   // [4 waves][G][TK]
-    char* kst = kl + text_part_bytes<D>(s.G, s.Nt);               // staged key blocks
-    const int KC = min(text_chunk_blocks<D>(s.G, s.Nt, kl_bytes), TB);
+    char* kst = kl + text_part_bytes<D>(G, s.Nt);               // staged key blocks
+    const int KC = min(text_chunk_blocks<D>(G, s.Nt, kl_bytes), TB);
     const int SB = lse_given ? 0 : (s.Ns + 15) >> 4;              // system-row blocks to normalise
 
     const int koff = (lane >> 4) * 8;
@@ -702,13 +702,13 @@ __device__ void text_pass_lds(const Shape& s, int bl, int kvh, const uint16_t* _
         for (int ks = 0; ks < GG::KSTEPS; ++ks) f[ks] = as_bf16x8(load16(src + ks * 32));
     };
     auto sys_item_q = [&](bf16x8 (&f)[GG::KSTEPS], int item) {
-        const int it = min(item, s.G * SB - 1);
+        const int it = min(item, G * SB - 1);
         load_q(f, it / SB, min((it % SB) * 16 + (lane & 15), s.Ns - 1));
     };
     // column items of a chunk starting at key block c0: row blocks rb >= c0 of every head
     auto col_item_q = [&](bf16x8 (&f)[GG::KSTEPS], int item, int c0) {
         const int nrb = TB - c0;
-        const int it = min(item, s.G * nrb - 1);
+        const int it = min(item, G * nrb - 1);
         load_q(f, it / nrb, min((c0 + it % nrb) * 16 + (lane & 15), s.Nt - 1));
     };
 
@@ -739,12 +739,12 @@ __device__ void text_pass_lds(const Shape& s, int bl, int kvh, const uint16_t* _
         }
     };
     stage(0, KC);
-    for (int x = tid; x < 4 * s.G * TK; x += kThreads) part[x] = 0.f;
+    for (int x = tid; x < 4 * G * TK; x += kThreads) part[x] = 0.f;
     __syncthreads();
 
     // system rows x system keys (all in the first chunk): row normalisers (C[key][row]: a
     // lane owns row i)
-    for (int item = wave; item < s.G * SB; item += 4) {
+    for (int item = wave; item < G * SB; item += 4) {
         const int g = item / SB, rb = item % SB;
         const int i = rb * 16 + (lane & 15);
         if (item != wave) sys_item_q(qs, item);
@@ -794,10 +794,10 @@ __device__ void text_pass_lds(const Shape& s, int bl, int kvh, const uint16_t* _
             __syncthreads();
         }
         const int nrb = TB - c0;
-        const int items = s.G * nrb;
+        const int items = G * nrb;
         auto consume = [&](const bf16x8 (&qf)[GG::KSTEPS], int item) {
             const int g = item / nrb, rb = c0 + item % nrb;
-            float* wpart = part + ((size_t)wave * s.G + g) * TK;
+            float* wpart = part + ((size_t)wave * G + g) * TK;
             float l2[4];
 #pragma unroll
             for (int jj = 0; jj < 4; ++jj)
@@ -835,11 +835,11 @@ __device__ void text_pass_lds(const Shape& s, int bl, int kvh, const uint16_t* _
         }
         __syncthreads();  // the chunk's keys are done with before the next is staged
     }
-    for (int x = tid; x < s.G * s.Nt; x += kThreads) {
+    for (int x = tid; x < G * s.Nt; x += kThreads) {
         const int g = x / s.Nt, j = x % s.Nt;
         float a = 0.f;
 #pragma unroll
-        for (int w = 0; w < 4; ++w) a += part[((size_t)w * s.G + g) * TK + j];
+        for (int w = 0; w < 4; ++w) a += part[((size_t)w * G + g) * TK + j];
         ws_colsum[(head0 + g) * s.Nt + j] = a;
     }
     __syncthreads();

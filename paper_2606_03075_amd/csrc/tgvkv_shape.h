@@ -27,14 +27,18 @@ struct RowPlan {
 
 RowPlan plan_question_rows(const Shape& s);
 
-// Score phases.
-hipError_t launch_score_stats(const Shape& s, const RowPlan& rp, const uint16_t* q_text,
-                              const uint16_t* k, float* lse, float* ws_vm, hipStream_t st);
+// Score phases.  ws_stat: the statistics of a sweep whose keys are split ([3][splits][B*L*H][N_q],
+// unused without a split); merge: turn them into lse and ws_vm here, else the text pass does.
+int stats_splits(const Shape& s, const RowPlan& rp);
+hipError_t launch_score_stats(const Shape& s, const RowPlan& rp, const uint16_t* q_text, const uint16_t* k,
+                              float* lse, float* ws_vm, float* ws_stat, bool merge, hipStream_t st);
 bool stats_text_eligible(const Shape& s, const RowPlan& rp);
 hipError_t launch_score_stats_text(const Shape& s, const RowPlan& rp, const uint16_t* q_text, const uint16_t* k,
                                    float* lse, float* ws_vm, float* ws_colsum, float* ws_vmh, hipStream_t st);
-hipError_t launch_score_text(const Shape& s, const uint16_t* q_text, const uint16_t* k, float* lse,
-                             const float* ws_vm, float* ws_colsum, float* ws_vmh, bool lse_given, hipStream_t st);
+// ws_stat: the split sweep's statistics to merge, or null (lse and ws_vm hold the rows' values).
+hipError_t launch_score_text(const Shape& s, const RowPlan& rp, const uint16_t* q_text, const uint16_t* k, float* lse,
+                             float* ws_vm, float* ws_colsum, float* ws_vmh, const float* ws_stat, bool lse_given,
+                             hipStream_t st);
 hipError_t launch_score_fin(const Shape& s, const float* ws_colsum, const float* ws_vmh, float* s_txt,
                             float* w_txt, float* tv_mass, bool with_mass, hipStream_t st);
 hipError_t launch_score_vision(const Shape& s, const RowPlan& rp, const uint16_t* q_text,

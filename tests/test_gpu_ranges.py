@@ -1,0 +1,72 @@
+"""Launch plans away from the benchmark's shapes: each test runs a plan at the sizes where it changes, against the oracle.
+
+Scores use gpu_util's tolerance (2e-3 relative; 32-bit sums are observed near 1e-6)."""
+
+import numpy as np
+import pytest
+
+from paper_2606_03075_amd import binding as bd
+from tests.gpu_util import assert_close_rel, dev_bf16, host, log, oracle_scores
+from workloads import make_prefill_tensors
+from workloads.configs import custom_config
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def lib():
+    import torch
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    return bd.load_library()
+
+
+def check_scores(cfg, head_mode=0, phase_lists=((bd.SCORE_ALL,),)):
+    """Scores of every (sequence, layer) against the oracle, for each way of asking for the phases."""
+    import torch
+    t = make_prefill_tensors(cfg, seed=5, names=("q_text", "k"))
+    ref = [[oracle_scores(t["q_text"][b, l], t["k"][b, l], cfg, head_mode) for l in range(cfg.layers)]
+           for b in range(cfg.batch)]
+    q, k = dev_bf16(t["q_text"]), dev_bf16(t["k"])
+    for phases in phase_lists:
+        buf = bd.EvictionBuffers(bd.problem_from(cfg), bd.make_opts(head_mode=head_mode), 0, 1)
+        for ph in phases:
+            if ph & bd.SCORE_LSE_IN:
+                lse = np.stack([[r["lse"] for r in row] for row in ref]).astype(np.float32)
+                buf.lse.copy_(torch.from_numpy(lse))
+            buf.score(q, k, ph)
+        torch.cuda.synchronize()
+        for b in range(cfg.batch):
+            for l in range(cfg.layers):
+                r = ref[b][l]
+                assert_close_rel("lse", host(buf.lse[b, l]), r["lse"], atol=1e-4)
+                for n in ("s_txt", "w_txt", "tv_mass", "s_vis"):
+                    assert_close_rel(n, host(getattr(buf, n)[b, l]), r[n])
+
+
+SPLIT_STATS = {
+    # 12 and 11 key tiles of one row slot per wave: the shortest split sweep and the longest whole one
+    "short_12_tiles": dict(heads_q=4, heads_kv=4, n_sys=5, n_vis=690, n_qst=50),
+    "whole_11_tiles": dict(heads_q=4, heads_kv=4, n_sys=5, n_vis=650, n_qst=49),
+    # 21 row blocks, six slots: 6 key tiles, the last of a single key
+    "gqa7_6_tiles": dict(heads_q=14, heads_kv=2, n_sys=17, n_vis=256, n_qst=48),
+    # shares that hold no vision key, or nothing but masked question keys for the early rows
+    "question_shares": dict(heads_q=2, heads_kv=2, n_sys=130, n_vis=70, n_qst=700),
+    "system_shares": dict(heads_q=2, heads_kv=2, n_sys=700, n_vis=70, n_qst=20),
+    # several row groups per unit, each split; the text pass per query head in chunks of key blocks
+    "row_groups": dict(heads_q=16, heads_kv=1, n_sys=40, n_vis=300, n_qst=160),
+    # text rows that do not fit the staged text pass
+    "long_text_split": dict(heads_q=2, heads_kv=1, n_sys=10, n_vis=100, n_qst=4000, layers=1),
+    # the most shares, and head_dim 64 with no system text
+    "many_shares": dict(heads_q=3, heads_kv=1, n_sys=9, n_vis=6800, n_qst=33),
+    "d64": dict(heads_q=8, heads_kv=2, head_dim=64, n_sys=0, n_vis=900, n_qst=19),
+}
+
+
+@pytest.mark.parametrize("name", sorted(SPLIT_STATS))
+def test_split_statistics(lib, name):
+    """The statistics sweep with its keys split over workgroups, merged by the text pass (both phases in
+    one call) and by the merge kernel (statistics alone, then text)."""
+    log(f"split statistics {name}")
+    cfg = custom_config(name=name, **dict(dict(batch=1, layers=2), **SPLIT_STATS[name]))
+    check_scores(cfg, 0, ((bd.SCORE_ALL,), (bd.SCORE_STATS, bd.SCORE_TEXT, bd.SCORE_VISION)))
