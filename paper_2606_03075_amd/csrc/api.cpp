@@ -200,7 +200,9 @@ const char* tgvkv_status_string(tgvkv_status st) {
 size_t tgvkv_workspace_size(const tgvkv_problem* problem, const tgvkv_opts* opts, int32_t which) {
     Shape s;
     if (make_shape(problem, opts, &s) != TGVKV_OK) return 0;
-    if (which == TGVKV_CALL_SCORE) return score_workspace(s, tgvkv::plan_question_rows(s), nullptr).bytes;
+    if (which == TGVKV_CALL_SCORE)  // enough for either order of sums
+        return std::max(score_workspace(s, tgvkv::plan_question_rows(s, false), nullptr).bytes,
+                        score_workspace(s, tgvkv::plan_question_rows(s, true), nullptr).bytes);
     if (which == TGVKV_CALL_DECODE) return decode_workspace_bytes(s);
     return 0;
 }
@@ -213,10 +215,11 @@ tgvkv_status tgvkv_score(const tgvkv_problem* problem, const tgvkv_opts* opts, i
     tgvkv_status st = make_shape(problem, opts, &s);
     if (st != TGVKV_OK) return st;
     const bool lse_in = (phases & TGVKV_SCORE_LSE_IN) != 0;
-    phases &= ~TGVKV_SCORE_LSE_IN;
+    const bool one_order = (phases & TGVKV_SCORE_ONE_ORDER) != 0;
+    phases &= ~(TGVKV_SCORE_LSE_IN | TGVKV_SCORE_ONE_ORDER);
     if (phases < 1 || phases > TGVKV_SCORE_ALL) return TGVKV_E_INVAL;
     // given normalisers: text and vision scores and the TV mass in one pass, for every layer
-    if (lse_in && (phases != (TGVKV_SCORE_TEXT | TGVKV_SCORE_VISION) || budgets_or_null != nullptr))
+    if (lse_in && (phases != (TGVKV_SCORE_TEXT | TGVKV_SCORE_VISION) || budgets_or_null != nullptr || one_order))
         return TGVKV_E_INVAL;
     if (lse_in && (int64_t)s.B * s.L * s.H * ((s.Nt + 15) / 16) > kMaxBlocks) return TGVKV_E_UNSUPPORTED;
     if (s.B == 0) return TGVKV_OK;
@@ -228,7 +231,7 @@ tgvkv_status tgvkv_score(const tgvkv_problem* problem, const tgvkv_opts* opts, i
     if ((phases & TGVKV_SCORE_VISION) && s.Nv > 0 && (s_vis == nullptr || (text_rows && w_txt == nullptr)))
         return TGVKV_E_INVAL;
     if (!aligned16(q_text) || !aligned16(k)) return TGVKV_E_INVAL;
-    const RowPlan rp = tgvkv::plan_question_rows(s);
+    const RowPlan rp = tgvkv::plan_question_rows(s, one_order);
     if ((int64_t)s.B * s.L * s.Hkv * std::max(rp.rowgroups, 1) > kMaxBlocks) return TGVKV_E_UNSUPPORTED;
     const ScoreWs need = score_workspace(s, rp, nullptr);
     if (workspace == nullptr || workspace_bytes < need.bytes) return TGVKV_E_WORKSPACE;

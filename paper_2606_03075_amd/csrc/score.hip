@@ -60,7 +60,7 @@ __device__ __forceinline__ void merge_row(const float* __restrict__ ws_stat, siz
 // unit leaves most of the chip idle, so the keys are split over nsplit workgroups (stats_splits);
 // the shares' statistics are merged by the text pass or by score_stats_merge.
 template <int D, int NSLOT, int KS>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(NSLOT >= 6 ? 2 : 1))) void score_stats_kernel(Shape s, int rowgroups,
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(NSLOT >= 6 ? 2 : NSLOT == 3 ? 3 : 1))) void score_stats_kernel(Shape s, int rowgroups,
                                                                const uint16_t* __restrict__ q_text,
                                                                const uint16_t* __restrict__ k,
                                                                float* __restrict__ lse,
@@ -141,7 +141,9 @@ constexpr bool kQregsText = NSLOT == 4 && KS == 1;
 // With four row slots the kernel is held to 168 registers, 3 waves per SIMD: it then spills
 // 96 bytes a lane, all outside the sweep's tile loops (at its phase changes and in the text
 // pass), and at the 13B stress shape it took 6.84 ms against 7.21-7.25 ms at 2 waves per SIMD.
-template <int D, int NSLOT, int KS>
+// QREGS: a kernel of its own for text mode 2, without the other modes' code: their calls beside the
+// spills at 168 registers cost the 13B stress shape 5 %.
+template <int D, int NSLOT, int KS, bool QREGS = false>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(NSLOT == 4 ? 3 : 1))) void
 score_stats_text_kernel(Shape s, const uint16_t* __restrict__ q_text, const uint16_t* __restrict__ k,
                         float* __restrict__ lse, float* __restrict__ ws_vm, float* __restrict__ ws_colsum,
@@ -166,7 +168,7 @@ score_stats_text_kernel(Shape s, const uint16_t* __restrict__ q_text, const uint
     // [G][N_t] normalisers (base 2), then [G][N_q] vision masses: in the dynamic LDS area
     // (text mode 2, whose text pass streams keys through the tiles), else in the freed tiles
     extern __shared__ float tarea[];
-    float* lse2s = text_mode == 2 ? tarea : reinterpret_cast<float*>(&tiles[0][0]);
+    float* lse2s = QREGS ? tarea : reinterpret_cast<float*>(&tiles[0][0]);
     float* vms = lse2s + (size_t)s.G * s.Nt;
     if (kp == 0 && lane < 16) {
 #pragma unroll
@@ -193,15 +195,12 @@ score_stats_text_kernel(Shape s, const uint16_t* __restrict__ q_text, const uint
         for (int off = 32; off > 0; off >>= 1) a += shfl_xor(a, off);
         if ((tid & 63) == 0) ws_vmh[head0 + g] = a;
     }
-    if constexpr (kQregsText<NSLOT, KS>) {
-        if (text_mode == 2) {
-            // the question rows' fragments are still in registers: only text keys are loaded
-            text_pass_qregs<D, NSLOT, KS>(s, bl, kvh, q_text, k, lse, qf, lse2s, vms + (size_t)s.G * s.Nq, tiles,
-                                          ws_colsum);
-            return;
-        }
-    }
-    if (text_mode == 1) {
+    if constexpr (QREGS) {
+        static_assert(kQregsText<NSLOT, KS>, "row plan without text mode 2");
+        // the question rows' fragments are still in registers: only text keys are loaded
+        text_pass_qregs<D, NSLOT, KS>(s, bl, kvh, q_text, k, lse, qf, lse2s, vms + (size_t)s.G * s.Nq, tiles,
+                                      ws_colsum);
+    } else if (text_mode == 1) {
         // the unit's text keys go into the freed tiles after the normalisers and masses
         const size_t off = ((size_t)s.G * (s.Nt + s.Nq) * sizeof(float) + 15) & ~(size_t)15;
         text_pass_lds<D>(s, bl, kvh, 0, s.G, q_text, k, lse, lse2s, &tiles[0][0] + off,
@@ -221,7 +220,7 @@ __global__ __launch_bounds__(kThreads) void score_text_kernel(Shape s, const uin
                                                               float* __restrict__ ws_colsum,
                                                               float* __restrict__ ws_vmh, int lse_given, int hsplit,
                                                               long long kl_bytes, const float* __restrict__ ws_stat,
-                                                              int nsplit) {
+                                                              int nsplit, int one_order) {
     // [G][N_t] row normalisers, base-2 units; with kl_bytes > 0, then the staged text pass's
     // LDS (text_pass_lds), 16-byte aligned
     extern __shared__ float lse2s[];
@@ -249,8 +248,15 @@ __global__ __launch_bounds__(kThreads) void score_text_kernel(Shape s, const uin
             lse2s[g * s.Nt + s.Ns + qi] = ln * kLog2e;
         }
         __syncthreads();
-        // per query head: the sum of its question rows' vision masses (one wave per head)
-        for (int g = tid >> 6; g < G; g += kThreads / 64) {
+        // per query head: the sum of its question rows' vision masses (one wave per head; in row
+        // order when one order of sums is asked for)
+        if (one_order) {
+            if (tid < G) {
+                float a = 0.f;
+                for (int qi = 0; qi < s.Nq; ++qi) a += ws_vm[(head0 + tid) * s.Nq + qi];
+                ws_vmh[head0 + tid] = a;
+            }
+        } else for (int g = tid >> 6; g < G; g += kThreads / 64) {
             float a = 0.f;
             for (int qi = tid & 63; qi < s.Nq; qi += 64) a += ws_vm[(head0 + g) * s.Nq + qi];
 #pragma unroll
@@ -453,7 +459,9 @@ __global__ __launch_bounds__(kThreads) void score_vis_reduce_kernel(Shape s, int
         else if (rp.ks == 2) hipLaunchKernelGGL((KERNEL<D, 2, 2>), __VA_ARGS__);                  \
         else if (rp.nslot == 1) hipLaunchKernelGGL((KERNEL<D, 1, 1>), __VA_ARGS__);               \
         else if (rp.nslot == 2) hipLaunchKernelGGL((KERNEL<D, 2, 1>), __VA_ARGS__);               \
+        else if (rp.nslot == 3) hipLaunchKernelGGL((KERNEL<D, 3, 1>), __VA_ARGS__);               \
         else if (rp.nslot == 4) hipLaunchKernelGGL((KERNEL<D, 4, 1>), __VA_ARGS__);               \
+        else if (rp.nslot == 5) hipLaunchKernelGGL((KERNEL<D, 5, 1>), __VA_ARGS__);               \
         else hipLaunchKernelGGL((KERNEL<D, 6, 1>), __VA_ARGS__);                                  \
     } while (0)
 
@@ -464,7 +472,9 @@ __global__ __launch_bounds__(kThreads) void score_vis_reduce_kernel(Shape s, int
         else if (rp.ks == 2) hipLaunchKernelGGL((KERNEL<D, 2, 2, M>), __VA_ARGS__);                       \
         else if (rp.nslot == 1) hipLaunchKernelGGL((KERNEL<D, 1, 1, M>), __VA_ARGS__);                    \
         else if (rp.nslot == 2) hipLaunchKernelGGL((KERNEL<D, 2, 1, M>), __VA_ARGS__);                    \
+        else if (rp.nslot == 3) hipLaunchKernelGGL((KERNEL<D, 3, 1, M>), __VA_ARGS__);                    \
         else if (rp.nslot == 4) hipLaunchKernelGGL((KERNEL<D, 4, 1, M>), __VA_ARGS__);                    \
+        else if (rp.nslot == 5) hipLaunchKernelGGL((KERNEL<D, 5, 1, M>), __VA_ARGS__);                    \
         else hipLaunchKernelGGL((KERNEL<D, 6, 1, M>), __VA_ARGS__);                                       \
     } while (0)
 
@@ -484,7 +494,9 @@ void with_vision_variant(int d, bool mass, const RowPlan& rp, int NB, F&& f) {
         else if (rp.ks == 2) f(dd, IC<2>{}, IC<2>{}, m);
         else if (rp.nslot == 1) f(dd, IC<1>{}, IC<1>{}, m);
         else if (rp.nslot == 2) f(dd, IC<2>{}, IC<1>{}, m);
+        else if (rp.nslot == 3) f(dd, IC<3>{}, IC<1>{}, m);
         else if (rp.nslot == 4) f(dd, IC<4>{}, IC<1>{}, m);
+        else if (rp.nslot == 5) f(dd, IC<5>{}, IC<1>{}, m);
         else f(dd, IC<6>{}, IC<1>{}, m);
     };
     auto with_d = [&](auto m) {
@@ -522,19 +534,35 @@ int resident_workgroups(const void* kernel, size_t dyn_lds) {
 // query head.
 constexpr long long kHeadSplitUnits = 512;
 
-RowPlan plan_question_rows(const Shape& s) {
+RowPlan plan_question_rows(const Shape& s, bool one_order) {
     const int QB = (s.Nq + 15) / 16;
     const int NB = s.G * QB;
     RowPlan rp;
-    if (NB <= 1) { rp.nslot = 1; rp.ks = 4; }
-    else if (NB == 2) { rp.nslot = 1; rp.ks = 2; }
-    else if (NB == 3) { rp.nslot = 1; rp.ks = 1; }  // the vision sweep runs these as (2, 2)
-    else if (NB <= 4) { rp.nslot = 1; rp.ks = 1; }
-    else if (NB <= 8) { rp.nslot = 2; rp.ks = 1; }
-    else if (NB <= 16) { rp.nslot = 4; rp.ks = 1; }
-    else { rp.nslot = 6; rp.ks = 1; }
-    const int per_group = (4 / rp.ks) * rp.nslot;
-    rp.rowgroups = NB > 0 ? (NB + per_group - 1) / per_group : 0;
+    rp.one_order = one_order;
+    // up to four row slots' worth of blocks: with one or two blocks the waves split each key tile
+    // instead (three and four blocks: the vision sweep has launch shapes of its own)
+    if (NB <= 4) {
+        rp.nslot = 1;
+        rp.ks = NB <= 1 ? 4 : NB == 2 ? 2 : 1;
+        rp.rowgroups = NB > 0 ? 1 : 0;
+        return rp;
+    }
+    // the fewest row groups of at most 4 waves x 6 slots (each group reads the unit's keys), the
+    // blocks dealt evenly over them, and no more slots per wave than that takes: an empty slot
+    // costs the statistics sweep as much as a full one.  Statistics (with the text pass where it is
+    // fused) and vision sweep, against slot counts of 2, 4 or 6 filled from the first group on:
+    // 12 blocks 3 slots 626 + 473 against 4 slots 793 + 449 us (80 units of 40 heads, 2215 keys);
+    // 20 blocks 5 slots 400 + 335 against 6 slots 426 + 374; 28 blocks 2 x 14 389 + 336 against
+    // 24 + 4 418 + 435; 21 blocks as 2 x 11 instead of one group: 955 + 944 against 841 + 794.
+    rp.rowgroups = (NB + 23) / 24;
+    rp.ks = 1;
+    if (one_order) {
+        // the order of sums that retained sets are taken from stays as it was: 2, 4 or 6 slots,
+        // filled from the first group on
+        rp.nslot = NB <= 8 ? 2 : NB <= 16 ? 4 : 6;
+        return rp;
+    }
+    rp.nslot = ((NB + rp.rowgroups - 1) / rp.rowgroups + 3) / 4;
     return rp;
 }
 
@@ -553,8 +581,8 @@ constexpr int kMaxShares = 32;
 int stats_splits(const Shape& s, const RowPlan& rp) {
     const long long units = (long long)s.B * s.L * s.Hkv * rp.rowgroups;
     const int tiles = (s.N + kTile - 1) / kTile;
-    if (units <= 0 || tiles < (rp.nslot >= 4 ? 6 : 12)) return 1;
-    const int per_cu = rp.nslot == 1 ? 4 : rp.nslot == 2 ? 3 : 2;
+    if (rp.one_order || units <= 0 || tiles < (rp.nslot >= 4 ? 6 : 12)) return 1;
+    const int per_cu = rp.nslot == 1 ? 4 : rp.nslot <= 3 ? 3 : 2;
     const int n = (int)std::min<long long>(std::min<long long>(256 * per_cu / units, tiles / kMinShareTiles), kMaxShares);
     if (n <= 1) return 1;
     const int per = (tiles + n - 1) / n;  // tiles per share; no share is empty
@@ -602,14 +630,22 @@ hipError_t launch_score_stats_text(const Shape& s, const RowPlan& rp, const uint
     const int occupancy = rp.nslot == 1 ? 4 : rp.nslot == 2 ? 3 : rp.nslot == 4 ? 3 : 2;
     const bool qregs = rp.nslot == 4 && rp.ks == 1 && s.Ns <= 2 * kTile && area <= 163840 / occupancy - tile_bytes;
     const long long head = ((long long)s.G * (s.Nt + s.Nq) * 4 + 15) / 16 * 16;
-    const size_t dyn = qregs ? (size_t)area : 0;
+    if (qregs) {
+        if (s.D == 128)
+            hipLaunchKernelGGL((score_stats_text_kernel<128, 4, 1, true>), grid, block, (size_t)area, st, s, q_text, k,
+                               lse, ws_vm, ws_colsum, ws_vmh, 2);
+        else
+            hipLaunchKernelGGL((score_stats_text_kernel<64, 4, 1, true>), grid, block, (size_t)area, st, s, q_text, k,
+                               lse, ws_vm, ws_colsum, ws_vmh, 2);
+        return hipGetLastError();
+    }
     if (s.D == 128) {
-        const int mode = qregs ? 2 : text_lds_fits<128>(s.G, s.Ns, s.Nt, tile_bytes - head) ? 1 : 0;
-        TGVKV_ROWPLAN_DISPATCH(score_stats_text_kernel, 128, rp, grid, block, dyn, st, s, q_text, k, lse, ws_vm,
+        const int mode = text_lds_fits<128>(s.G, s.Ns, s.Nt, tile_bytes - head) ? 1 : 0;
+        TGVKV_ROWPLAN_DISPATCH(score_stats_text_kernel, 128, rp, grid, block, 0, st, s, q_text, k, lse, ws_vm,
                                ws_colsum, ws_vmh, mode);
     } else {
-        const int mode = qregs ? 2 : text_lds_fits<64>(s.G, s.Ns, s.Nt, tile_bytes - head) ? 1 : 0;
-        TGVKV_ROWPLAN_DISPATCH(score_stats_text_kernel, 64, rp, grid, block, dyn, st, s, q_text, k, lse, ws_vm,
+        const int mode = text_lds_fits<64>(s.G, s.Ns, s.Nt, tile_bytes - head) ? 1 : 0;
+        TGVKV_ROWPLAN_DISPATCH(score_stats_text_kernel, 64, rp, grid, block, 0, st, s, q_text, k, lse, ws_vm,
                                ws_colsum, ws_vmh, mode);
     }
     return hipGetLastError();
@@ -622,7 +658,7 @@ hipError_t launch_score_text(const Shape& s, const RowPlan& rp, const uint16_t* 
     if (nblk == 0 || s.Nt == 0) return hipSuccess;
     // with few units, one workgroup per query head: each stages the unit's text keys again (from
     // cache), but a unit's heads no longer follow one another in the same four waves
-    const int hsplit = s.G > 1 && nblk <= kHeadSplitUnits ? s.G : 1;
+    const int hsplit = s.G > 1 && nblk <= kHeadSplitUnits && !rp.one_order ? s.G : 1;
     const int G = s.G / hsplit;
     // the unit's text keys staged in LDS (text_pass_lds; in chunks of key blocks when they do not
     // all fit beside the normalisers within 64 KB): against one wave per (unit, head, 16-key block)
@@ -633,7 +669,7 @@ hipError_t launch_score_text(const Shape& s, const RowPlan& rp, const uint16_t* 
         (s.D == 128 ? text_part_bytes<128>(G, s.Nt) : text_part_bytes<64>(G, s.Nt)) + 16LL * TB * (2 * s.D + 16),
         65536 - head);
     const int sys = lse_given ? 0 : s.Ns;
-    const bool staged = kl > 0 && (s.D == 128 ? text_lds_fits<128>(G, sys, s.Nt, kl) : text_lds_fits<64>(G, sys, s.Nt, kl));
+    const bool staged = kl > 0 && !rp.one_order && (s.D == 128 ? text_lds_fits<128>(G, sys, s.Nt, kl) : text_lds_fits<64>(G, sys, s.Nt, kl));
     if (lse_given && !staged) {
         const long long items = nblk * s.G * TB;
         if (s.D == 128)
@@ -649,10 +685,10 @@ hipError_t launch_score_text(const Shape& s, const RowPlan& rp, const uint16_t* 
     const int nsplit = ws_stat != nullptr ? stats_splits(s, rp) : 1;
     if (s.D == 128)
         hipLaunchKernelGGL(score_text_kernel<128>, grid, block, lds, st, s, q_text, k, lse, ws_vm, ws_colsum, ws_vmh,
-                           (int)lse_given, hsplit, staged ? kl : 0LL, ws_stat, nsplit);
+                           (int)lse_given, hsplit, staged ? kl : 0LL, ws_stat, nsplit, (int)rp.one_order);
     else
         hipLaunchKernelGGL(score_text_kernel<64>, grid, block, lds, st, s, q_text, k, lse, ws_vm, ws_colsum, ws_vmh,
-                           (int)lse_given, hsplit, staged ? kl : 0LL, ws_stat, nsplit);
+                           (int)lse_given, hsplit, staged ? kl : 0LL, ws_stat, nsplit, (int)rp.one_order);
     return hipGetLastError();
 }
 
@@ -712,7 +748,7 @@ hipError_t launch_score_vision(const Shape& s, const RowPlan& rp, const uint16_t
     } else if (rp.nslot == 1 && rp.ks == 1 && (s.G * ((s.Nq + 15) / 16)) == 3) {
         // three 16-row blocks per unit: two slots over half of each key tile (same row groups);
         // at the LLaVA-1.5 shape 43 us against 46-48 us for the four-slot shape below
-        const RowPlan r2{2, 2, rp.rowgroups};
+        const RowPlan r2{2, 2, rp.rowgroups, rp.one_order};
         if (s.D == 128)
             TGVKV_ROWPLAN_DISPATCH_M(score_vision_kernel, 128, false, r2, grid, block, obytes, st, s, rp.rowgroups, q_text, k, lse, w_txt, budgets, vis_threshold, ws_part, ws_vm, out_tiles, deal);
         else

@@ -23,9 +23,10 @@ struct Shape {
 // (each up to NSLOT blocks) and, for few blocks, split each key tile into KS parts.
 struct RowPlan {
     int nslot, ks, rowgroups;
+    bool one_order;  // sums in an order set by the unit's shape alone (TGVKV_SCORE_ONE_ORDER)
 };
 
-RowPlan plan_question_rows(const Shape& s);
+RowPlan plan_question_rows(const Shape& s, bool one_order);
 
 // Score phases.  ws_stat: the statistics of a sweep whose keys are split ([3][splits][B*L*H][N_q],
 // unused without a split); merge: turn them into lse and ws_vm here, else the text pass does.

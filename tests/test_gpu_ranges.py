@@ -70,3 +70,42 @@ def test_split_statistics(lib, name):
     log(f"split statistics {name}")
     cfg = custom_config(name=name, **dict(dict(batch=1, layers=2), **SPLIT_STATS[name]))
     check_scores(cfg, 0, ((bd.SCORE_ALL,), (bd.SCORE_STATS, bd.SCORE_TEXT, bd.SCORE_VISION)))
+
+
+# 16-row blocks per KV head, (query heads, question rows): the edges of every slot count and of the row groups
+ROW_PLANS = {5: (5, 16), 8: (4, 30), 9: (3, 48), 12: (4, 33), 13: (13, 9), 16: (16, 16), 17: (1, 260), 20: (4, 80),
+             21: (7, 48), 24: (12, 20), 25: (5, 75), 28: (7, 64), 33: (11, 48), 49: (7, 100)}
+
+
+@pytest.mark.parametrize("head_dim", [64, 128])
+@pytest.mark.parametrize("blocks", sorted(ROW_PLANS))
+def test_row_plans(lib, blocks, head_dim):
+    """Question rows dealt over row groups and row slots, statistics and vision sweep, with and without given
+    normalisers (whose sweep also sums each row)."""
+    heads, nq = ROW_PLANS[blocks]
+    assert heads * ((nq + 15) // 16) == blocks
+    log(f"row plan {blocks} blocks d{head_dim}")
+    cfg = custom_config(name=f"nb{blocks}", batch=1, layers=1, heads_q=2 * heads, heads_kv=2, head_dim=head_dim, n_sys=7,
+                        n_vis=150, n_qst=nq)
+    check_scores(cfg, 1, ((bd.SCORE_ALL,), (bd.SCORE_TEXT | bd.SCORE_VISION | bd.SCORE_LSE_IN,)))
+
+
+def test_one_order_in_any_batch(lib):
+    """With ONE_ORDER a sequence's scores are the same bits alone, where other calls split its keys over workgroups,
+    and in a batch; with given normalisers the flag is refused."""
+    import torch
+    log("one order")
+    shape = dict(layers=3, heads_q=14, heads_kv=2, n_sys=9, n_vis=900, n_qst=60)
+    t = make_prefill_tensors(custom_config(batch=80, **shape), seed=2, names=("q_text", "k"), seqs=range(2))
+    q, k = (dev_bf16(t[n]).repeat(40, 1, 1, 1, 1) for n in ("q_text", "k"))
+
+    def scores(batch):
+        buf = bd.EvictionBuffers(bd.problem_from(custom_config(batch=batch, **shape)), None, 0, 1)
+        buf.score(q[:batch].contiguous(), k[:batch].contiguous(), bd.SCORE_ALL | bd.SCORE_ONE_ORDER)
+        return buf
+    one, many = scores(1), scores(80)
+    for n in ("lse", "s_txt", "w_txt", "tv_mass", "s_vis"):
+        a, b = getattr(one, n), getattr(many, n)
+        assert torch.equal(a[0], b[0]) and torch.equal(b[0], b[78]) and torch.equal(b[1], b[79]), n
+    with pytest.raises(bd.TgvkvError):
+        one.score(q[:1], k[:1], bd.SCORE_TEXT | bd.SCORE_VISION | bd.SCORE_LSE_IN | bd.SCORE_ONE_ORDER)
