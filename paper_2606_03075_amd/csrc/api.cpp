@@ -246,8 +246,8 @@ tgvkv_status tgvkv_score(const tgvkv_problem* problem, const tgvkv_opts* opts, i
         if (e == hipSuccess) e = tgvkv::launch_score_fin(s, w.colsum, w.vmh, s_txt, w_txt, tv_mass, false, stream);
         if (e == hipSuccess)
             e = tgvkv::launch_score_vision(s, rp, q, kk, lse, w_txt, nullptr, vthr, w.part, w.vm, stream);
-        if (e == hipSuccess) e = tgvkv::launch_score_vis_reduce(s, rp, w.part, nullptr, vthr, s_vis, stream);
-        if (e == hipSuccess) e = tgvkv::launch_score_mass(s, rp, w.vm, w.vmh, tv_mass, stream);
+        if (e == hipSuccess)
+            e = tgvkv::launch_score_vis_reduce(s, rp, w.part, nullptr, vthr, s_vis, w.vm, tv_mass, stream);
         return hip_status(e);
     }
     const bool both = (phases & TGVKV_SCORE_STATS) && (phases & TGVKV_SCORE_TEXT);
@@ -263,7 +263,7 @@ tgvkv_status tgvkv_score(const tgvkv_problem* problem, const tgvkv_opts* opts, i
     }
     if ((phases & TGVKV_SCORE_VISION) && e == hipSuccess && s.Nv > 0) {
         e = tgvkv::launch_score_vision(s, rp, q, kk, lse, w_txt, budgets_or_null, vthr, w.part, nullptr, stream);
-        if (e == hipSuccess) e = tgvkv::launch_score_vis_reduce(s, rp, w.part, budgets_or_null, vthr, s_vis, stream);
+        if (e == hipSuccess) e = tgvkv::launch_score_vis_reduce(s, rp, w.part, budgets_or_null, vthr, s_vis, nullptr, nullptr, stream);
     }
     return hip_status(e);
 }

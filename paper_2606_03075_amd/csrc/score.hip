@@ -19,11 +19,10 @@
 //                 text->vision mass (Eq. (5)-(6));
 //   score_vision  sweep 2: question rows x vision keys, p = exp(z - lse),
 //                 column sums weighted by w~ (Eq. (8));
-//   score_vis_reduce  deterministic sum of the per-(KV head, row group) partials;
-//   score_mass    layer TV mass from per-row vision masses, when the caller gives
-//                 the rows' normalisers (from its prefill) and sweep 1 is skipped:
-//                 the vision sweep then also yields each row's vision mass, so K
-//                 is read once.
+//   score_vis_reduce  deterministic sum of the per-(KV head, row group) partials; when
+//                 the caller gives the rows' normalisers (from its prefill) and sweep 1 is
+//                 skipped, the vision sweep also yields each row's vision mass, so K is read
+//                 once, and this launch forms the layers' TV masses from them.
 //
 // These kernels serve phase-by-phase calls (and the vision pass restricted to
 // layers whose budget reaches past the text).
@@ -132,19 +131,20 @@ __global__ __launch_bounds__(kThreads) void score_stats_merge_kernel(Shape s, co
 // the text pass through LDS.  The row statistics are bit-identical to
 // score_stats'; the text pass stages the unit's text keys in the freed tiles
 // when they fit (a different summation order of the same column sums).
-// Row plans whose statistics+text kernel has text mode 2 (text_pass_qregs): with four row
-// slots per wave the sweep sets the kernel's register count, and the pass fits beside it;
-// with fewer slots it would cost occupancy, with six it would spill.
+// Row plans whose statistics+text kernel has text mode 2 (text_pass_qregs): with three or four
+// row slots per wave the sweep sets the kernel's register count, and the pass fits beside it;
+// with fewer slots it would cost occupancy, with more it would spill.  With three slots (11 row
+// blocks, 262 text rows of 450) 523 us against 721 us for text mode 1.
 template <int NSLOT, int KS>
-constexpr bool kQregsText = NSLOT == 4 && KS == 1;
+constexpr bool kQregsText = (NSLOT == 3 || NSLOT == 4) && KS == 1;
 
-// With four row slots the kernel is held to 168 registers, 3 waves per SIMD: it then spills
+// With three or four row slots the kernel is held to 168 registers, 3 waves per SIMD: it then spills
 // 96 bytes a lane, all outside the sweep's tile loops (at its phase changes and in the text
 // pass), and at the 13B stress shape it took 6.84 ms against 7.21-7.25 ms at 2 waves per SIMD.
 // QREGS: a kernel of its own for text mode 2, without the other modes' code: their calls beside the
 // spills at 168 registers cost the 13B stress shape 5 %.
 template <int D, int NSLOT, int KS, bool QREGS = false>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(NSLOT == 4 ? 3 : 1))) void
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(NSLOT == 3 || NSLOT == 4 ? 3 : 1))) void
 score_stats_text_kernel(Shape s, const uint16_t* __restrict__ q_text, const uint16_t* __restrict__ k,
                         float* __restrict__ lse, float* __restrict__ ws_vm, float* __restrict__ ws_colsum,
                         float* __restrict__ ws_vmh, int text_mode) {
@@ -301,36 +301,6 @@ __global__ __launch_bounds__(kThreads) void score_fin_kernel(Shape s, const floa
                    tv_mass, red, with_mass != 0);
 }
 
-// Layer TV mass (Eq. (5)-(6)) from per-row vision masses, in the same order as the
-// two-sweep path: per head over question rows, then the mean over heads.
-// ws_vm holds one row-mass partial per share of the vision keys ([vsplit][B*L*H][N_q]); a
-// row's shares are added first, in share order.
-__global__ __launch_bounds__(kThreads) void score_mass_kernel(Shape s, const float* __restrict__ ws_vm,
-                                                              float* __restrict__ ws_vmh,
-                                                              float* __restrict__ tv_mass, int vsplit) {
-    const int bl = blockIdx.x;
-    const size_t share = (size_t)s.B * s.L * s.H * s.Nq;
-    for (int h = threadIdx.x; h < s.H; h += kThreads) {
-        float a = 0.f;
-        if (s.Nv > 0) {  // with no vision keys the vision sweep does not run and every mass is 0
-            const float* vm = ws_vm + ((size_t)bl * s.H + h) * s.Nq;
-            for (int qi = 0; qi < s.Nq; ++qi) {
-                float r = vm[qi];
-                for (int sp = 1; sp < vsplit; ++sp) r += vm[sp * share + qi];
-                a += r;
-            }
-        }
-        ws_vmh[(size_t)bl * s.H + h] = a;
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        float a = 0.f;
-        if (s.Nt > 0)
-            for (int h = 0; h < s.H; ++h) a += ws_vmh[(size_t)bl * s.H + h];
-        tv_mass[bl] = a / (float)s.H;
-    }
-}
-
 // How the vision sweep's workgroups are dealt out: each (unit, row group) has vsplit shares
 // of its vision keys; workgroup b < nfull takes share b whole, and the shares after those are
 // each cut into `pieces` workgroups.  The cut shares are the last ones dispatched: they would
@@ -427,14 +397,59 @@ __global__ __launch_bounds__(kThreads) void score_vision_kernel(Shape s, int row
     }
 }
 
+// Layer TV mass (Eq. (5)-(6)) from per-row vision masses, by one workgroup: the mean over the query
+// heads of the sum of their question rows' masses, i.e. one sum over the layer's H * N_q rows.  ws_vm
+// holds one row-mass partial per share of the vision keys ([vsplit][B*L*H][N_q]).  The loads are
+// independent, eight in flight a thread; a thread per head, walking its rows one load after another,
+// took 10-20 us in a launch of its own.
+__device__ void layer_mass(const Shape& s, int bl, const float* __restrict__ ws_vm, float* __restrict__ tv_mass,
+                           int vsplit) {
+    __shared__ float wsum[kThreads / 64];
+    const int n = s.H * s.Nq;
+    const size_t share = (size_t)s.B * s.L * n;
+    float a[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    if (s.Nv > 0) {  // with no vision keys the vision sweep does not run and every mass is 0
+        for (int sp = 0; sp < vsplit; ++sp) {
+            const float* vm = ws_vm + sp * share + (size_t)bl * n;
+            int x = threadIdx.x;
+            for (; x + 7 * kThreads < n; x += 8 * kThreads) {
+#pragma unroll
+                for (int u = 0; u < 8; ++u) a[u] += vm[x + u * kThreads];
+            }
+#pragma unroll
+            for (int u = 0; u < 7; ++u)
+                if (x + u * kThreads < n) a[u] += vm[x + u * kThreads];
+        }
+    }
+    float t = ((a[0] + a[1]) + (a[2] + a[3])) + ((a[4] + a[5]) + (a[6] + a[7]));
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) t += shfl_xor(t, off);
+    if ((threadIdx.x & 63) == 0) wsum[threadIdx.x >> 6] = t;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        float m = 0.f;
+#pragma unroll
+        for (int w = 0; w < kThreads / 64; ++w) m += wsum[w];
+        tv_mass[bl] = m / (float)s.H;
+    }
+}
+
+// Sums the (KV head, row group) partials of every vision key; with ws_vm (row masses collected by
+// the sweep) the workgroups past the keys' (blockIdx.x == nx) form the layers' TV masses.
 __global__ __launch_bounds__(kThreads) void score_vis_reduce_kernel(Shape s, int rowgroups,
                                                                     const float* __restrict__ ws_part,
                                                                     const int32_t* __restrict__ budgets,
                                                                     int vis_threshold,
-                                                                    float* __restrict__ s_vis) {
+                                                                    float* __restrict__ s_vis, int nx,
+                                                                    const float* __restrict__ ws_vm,
+                                                                    float* __restrict__ tv_mass, int vsplit) {
     const int j = blockIdx.x * kThreads + threadIdx.x;
     const int gi = blockIdx.y % s.ngroups;
     const int bl = blockIdx.y / s.ngroups;
+    if (blockIdx.x == nx) {
+        if (gi == 0) layer_mass(s, bl, ws_vm, tv_mass, vsplit);
+        return;
+    }
     if (j >= s.Nv) return;
     if (budgets != nullptr && budgets[bl] <= vis_threshold) return;
     const int kv0 = s.head_mode == 0 ? 0 : gi;
@@ -627,16 +642,18 @@ hipError_t launch_score_stats_text(const Shape& s, const RowPlan& rp, const uint
     // keys' blocks fit there; else mode 0 reads them from memory.
     const long long tile_bytes = 2LL * kTile * (2 * s.D + 16);
     const long long area = text_area_floats(s.G, s.Nt, s.Nq) * (long long)sizeof(float);
-    const int occupancy = rp.nslot == 1 ? 4 : rp.nslot == 2 ? 3 : rp.nslot == 4 ? 3 : 2;
-    const bool qregs = rp.nslot == 4 && rp.ks == 1 && s.Ns <= 2 * kTile && area <= 163840 / occupancy - tile_bytes;
+    const int occupancy = rp.nslot == 1 ? 4 : rp.nslot <= 4 ? 3 : 2;
+    const bool qregs = (rp.nslot == 3 || rp.nslot == 4) && rp.ks == 1 && s.Ns <= 2 * kTile && area <= 163840 / occupancy - tile_bytes;
     const long long head = ((long long)s.G * (s.Nt + s.Nq) * 4 + 15) / 16 * 16;
     if (qregs) {
-        if (s.D == 128)
-            hipLaunchKernelGGL((score_stats_text_kernel<128, 4, 1, true>), grid, block, (size_t)area, st, s, q_text, k,
-                               lse, ws_vm, ws_colsum, ws_vmh, 2);
-        else
-            hipLaunchKernelGGL((score_stats_text_kernel<64, 4, 1, true>), grid, block, (size_t)area, st, s, q_text, k,
-                               lse, ws_vm, ws_colsum, ws_vmh, 2);
+        auto launch = [&](auto d, auto ns) {
+            hipLaunchKernelGGL((score_stats_text_kernel<decltype(d)::value, decltype(ns)::value, 1, true>), grid, block,
+                               (size_t)area, st, s, q_text, k, lse, ws_vm, ws_colsum, ws_vmh, 2);
+        };
+        if (s.D == 128 && rp.nslot == 3) launch(IC<128>{}, IC<3>{});
+        else if (s.D == 128) launch(IC<128>{}, IC<4>{});
+        else if (rp.nslot == 3) launch(IC<64>{}, IC<3>{});
+        else launch(IC<64>{}, IC<4>{});
         return hipGetLastError();
     }
     if (s.D == 128) {
@@ -702,12 +719,24 @@ hipError_t launch_score_fin(const Shape& s, const float* ws_colsum, const float*
 }
 
 int vision_splits(const Shape& s, const RowPlan& rp) {
-    // With few (unit, row group) workgroups the vision keys are split over several: at the
-    // Qwen2-VL shape (896 units, 2 workgroups per CU) two splits balance the last round
-    // (805 -> 740 us); at 4096 units a split only adds prologues.  The mass-collecting variant
-    // writes one row-mass partial per share, which score_mass adds.
+    // With few (unit, row group) workgroups the vision keys are split over several.  Below one round
+    // of resident workgroups (3 per CU up to four slots, else 2) the split fills one round, each
+    // share at least 3 key tiles: one video (112 units) in 4 shares 116 us against 125 us in 8
+    // (1.75 rounds); one layer of 128 units 32 -> 24.5 us.  Up to 2048 workgroups two rounds: at the
+    // Qwen2-VL shape (896 units, 2 workgroups per CU) two splits balance the last round (805 -> 740
+    // us); at 4096 units a split only adds prologues.  The mass-collecting variant writes one row-mass
+    // partial per share, which the reduction adds.
     const long long units = (long long)s.B * s.L * s.Hkv * rp.rowgroups;
-    return units <= 0 ? 1 : (int)std::min<long long>(std::max<long long>(2048 / units, 1), 4);
+    if (units <= 0) return 1;
+    const long long round = 256 * (rp.nslot <= 4 ? 3 : 2);
+    const int tiles = (s.Nv + kTile - 1) / kTile;
+    if (units * 2 <= round) {
+        const int n = (int)std::max<long long>(
+            std::min<long long>(std::min<long long>(round / units, tiles / kMinShareTiles), kMaxShares), 1);
+        const int per = (tiles + n - 1) / n;  // tiles per share; no share is empty
+        return per > 0 ? (tiles + per - 1) / per : 1;
+    }
+    return (int)std::min<long long>(std::max<long long>(2048 / units, 1), 4);
 }
 
 hipError_t launch_score_vision(const Shape& s, const RowPlan& rp, const uint16_t* q_text, const uint16_t* k,
@@ -734,7 +763,7 @@ hipError_t launch_score_vision(const Shape& s, const RowPlan& rp, const uint16_t
     // piece at least 4 key tiles); the mass-collecting sweep keeps one row-mass partial per share
     VisionDeal deal{vsplit, nsh, 1};
     const int slots = mass ? 0 : resident_workgroups(fn, obytes);
-    if (slots > 0 && nsh % slots != 0) {
+    if (slots > 0 && nsh > slots && nsh % slots != 0) {
         const long long r = nsh % slots;
         const int most = std::max(ntiles / 4, 1);
         const int pieces = (int)std::min<long long>((slots + r - 1) / r, most);
@@ -769,23 +798,17 @@ hipError_t launch_score_vision(const Shape& s, const RowPlan& rp, const uint16_t
     return hipGetLastError();
 }
 
-hipError_t launch_score_mass(const Shape& s, const RowPlan& rp, const float* ws_vm, float* ws_vmh, float* tv_mass,
-                             hipStream_t st) {
-    const long long nblk = (long long)s.B * s.L;
-    if (nblk == 0) return hipSuccess;
-    hipLaunchKernelGGL(score_mass_kernel, dim3((unsigned)nblk), dim3(kThreads), 0, st, s, ws_vm, ws_vmh, tv_mass,
-                       vision_splits(s, rp));
-    return hipGetLastError();
-}
-
 hipError_t launch_score_vis_reduce(const Shape& s, const RowPlan& rp, const float* ws_part, const int32_t* budgets,
-                                   int32_t vis_threshold, float* s_vis, hipStream_t st) {
+                                   int32_t vis_threshold, float* s_vis, const float* ws_vm, float* tv_mass,
+                                   hipStream_t st) {
     const long long ny = (long long)s.B * s.L * s.ngroups;
-    if (ny == 0 || s.Nv == 0) return hipSuccess;
+    const bool mass = ws_vm != nullptr;
+    const int nx = (s.Nv + kThreads - 1) / kThreads;
+    if (ny == 0 || nx + (int)mass == 0) return hipSuccess;
     // With no question rows there are no partials (rowgroups == 0) and every score is zero.
-    dim3 grid((s.Nv + kThreads - 1) / kThreads, (unsigned)ny);
+    dim3 grid((unsigned)(nx + (int)mass), (unsigned)ny);
     hipLaunchKernelGGL(score_vis_reduce_kernel, grid, dim3(kThreads), 0, st, s, rp.rowgroups, ws_part, budgets,
-                       vis_threshold, s_vis);
+                       vis_threshold, s_vis, nx, ws_vm, tv_mass, vision_splits(s, rp));
     return hipGetLastError();
 }
 

@@ -49,11 +49,10 @@ hipError_t launch_score_vision(const Shape& s, const RowPlan& rp, const uint16_t
 // Shares of the vision keys a unit's vision sweep is split over (the mass-collecting sweep
 // writes one row-mass partial per share).
 int vision_splits(const Shape& s, const RowPlan& rp);
-hipError_t launch_score_mass(const Shape& s, const RowPlan& rp, const float* ws_vm, float* ws_vmh, float* tv_mass,
-                             hipStream_t st);
+// ws_vm non-null: the sweep's row masses, from which this also forms tv_mass.
 hipError_t launch_score_vis_reduce(const Shape& s, const RowPlan& rp, const float* ws_part,
                                    const int32_t* budgets, int32_t vis_threshold, float* s_vis,
-                                   hipStream_t st);
+                                   const float* ws_vm, float* tv_mass, hipStream_t st);
 
 // Water-fills `total` over the layers with per-layer cap `cap_tokens` and floor
 // n_floor, then writes b_l = add + share (add = N_t in vision-only eviction), and,

@@ -72,6 +72,27 @@ def test_split_statistics(lib, name):
     check_scores(cfg, 0, ((bd.SCORE_ALL,), (bd.SCORE_STATS, bd.SCORE_TEXT, bd.SCORE_VISION)))
 
 
+SPLIT_VISION = {
+    # 3-tile shares, the last one ragged; shares of a row plan with its own vision launch shape; two row groups
+    "mha": dict(heads_q=4, heads_kv=4, n_sys=5, n_vis=1201, n_qst=50),
+    "three_blocks": dict(heads_q=4, heads_kv=4, n_sys=0, n_vis=449, n_qst=40),
+    "below_a_share": dict(heads_q=4, heads_kv=4, n_sys=3, n_vis=190, n_qst=20),
+    "gqa7_d64": dict(heads_q=14, heads_kv=2, head_dim=64, n_sys=3, n_vis=700, n_qst=50),
+    "most_shares": dict(heads_q=7, heads_kv=1, n_sys=16, n_vis=6500, n_qst=48),
+    "no_vision": dict(heads_q=4, heads_kv=2, n_sys=30, n_vis=0, n_qst=20),
+    "no_question": dict(heads_q=4, heads_kv=2, n_sys=30, n_vis=300, n_qst=0),
+}
+
+
+@pytest.mark.parametrize("name", sorted(SPLIT_VISION))
+def test_split_vision(lib, name):
+    """The vision sweep's keys split over workgroups, and with given normalisers the layers' masses from the shares'
+    row masses."""
+    log(f"split vision {name}")
+    cfg = custom_config(name=name, **dict(dict(batch=1, layers=2), **SPLIT_VISION[name]))
+    check_scores(cfg, 0, ((bd.SCORE_ALL,), (bd.SCORE_TEXT | bd.SCORE_VISION | bd.SCORE_LSE_IN,)))
+
+
 # 16-row blocks per KV head, (query heads, question rows): the edges of every slot count and of the row groups
 ROW_PLANS = {5: (5, 16), 8: (4, 30), 9: (3, 48), 12: (4, 33), 13: (13, 9), 16: (16, 16), 17: (1, 260), 20: (4, 80),
              21: (7, 48), 24: (12, 20), 25: (5, 75), 28: (7, 64), 33: (11, 48), 49: (7, 100)}
