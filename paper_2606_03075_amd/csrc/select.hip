@@ -4,18 +4,25 @@
 // positions first (first n_sink, last n_recent), then either the top text tokens
 // by s^T (the budget does not cover the remaining text) or all text and the top
 // vision tokens by s^V.  The top-k is an exact radix select on order-preserving
-// 32-bit keys (4 passes of 8 bits with an LDS histogram; the digit holding the
-// k-th key is found by a wave-wide scan of the histogram), which yields the k-th
-// largest key and how many of its ties to take; ties go to the lower position.
-// The retained positions are then emitted already in ascending order, with no sort:
-// each wave takes a contiguous run of 64-position groups, wave ballots count and rank
-// the ties and the kept positions, and the waves' counts, added across one barrier, give
-// each run the rank of its first tie and the output slot of its first kept position.
-// The workgroup has 1024 threads: the work is a few latency-bound rounds per
-// (sequence, layer, group), and there are few such units.  Without TPR (an ablation of Table 5)
-// all non-forced positions compete on one scale: text by s^T, vision by s^V times
-// a factor (N_t under TWR, whose weights sum to 1).  Candidate keys are read from global
-// memory once and kept in LDS when the row fits (N <= kLdsKeys).
+// 32-bit keys, which yields the k-th largest key and how many of its ties to take;
+// ties go to the lower position.  The retained positions are emitted already in
+// ascending order, with no sort: each wave takes a contiguous run of 64-position
+// groups, wave ballots count and rank the ties and the kept positions, and the waves'
+// counts, added across one barrier, give each run the rank of its first tie and the
+// output slot of its first kept position.  The workgroup has 1024 threads: the work is
+// a few latency-bound rounds per (sequence, layer, group), and there are few such units.
+// Without TPR (an ablation of Table 5) all non-forced positions compete on one scale:
+// text by s^T, vision by s^V times a factor (N_t under TWR, whose weights sum to 1).
+//
+// Rows up to kRegRow positions keep their keys in registers, in the emission's layout (a lane's
+// keys are its positions of the wave's groups): each score is read once, with every load of the
+// row in flight, and neither the select's passes nor the emission touch memory again.  The select
+// starts at the highest bit in which the row's keys differ and takes 11 bits a pass, so scores of
+// similar size spread over the bins at once (an 8-bit pass from the top puts nearly all of them in one
+// or two bins, whose LDS atomics then serialise); once at most 64 keys share the k-th key's
+// digits, one wave ranks them all against all.  Longer rows re-read the scores in four 8-bit
+// passes.  8256 positions, 224 rows: 28.6 -> 17.2 us; 2979 positions, 128 rows: 13.8 -> 9.1 us;
+// 651 positions, 32 rows: 7.5 -> 6.4 us (kernel trace).
 #include "tgvkv_device.h"
 #include "tgvkv_shape.h"
 
@@ -24,7 +31,9 @@ namespace {
 
 constexpr int kThreads = 1024;
 constexpr int kWaves = kThreads / 64;
-constexpr int kLdsKeys = 12288;  // 48 KB of LDS keys per workgroup
+constexpr int kRegGroups = 12;                       // 64-position groups per wave kept in registers
+constexpr int kRegRow = kRegGroups * kThreads;       // 12288 positions
+constexpr int kBits = 11, kBins = 1 << kBits;        // digits of the register select
 enum { MODE_FORCED = 0, MODE_TEXT = 1, MODE_VIS = 2, MODE_JOINT = 3 };
 constexpr uint32_t kNotCand = 0u;  // keys of real candidates have the top bit or are >= 1
 
@@ -42,13 +51,15 @@ struct RowCtx {
         if (mode == MODE_JOINT) return true;
         return mode == MODE_VIS ? is_vis(p) : !is_vis(p);
     }
-    // key of a candidate (only called when cand(p)); never kNotCand for finite scores.  The
-    // forced positions all get one key, so the ties-to-lower-position rule takes the first ones.
-    __device__ uint32_t key(int p) const {
+    // key of a candidate (only called when cand(p)) with score x; never kNotCand for finite scores.
+    // The forced positions all get one key, so the ties-to-lower-position rule takes the first ones.
+    __device__ uint32_t key_of(int p, float x) const {
         if (mode == MODE_FORCED) return 1u;
-        if (mode == MODE_VIS) return ordered_key(sv[p - Ns]);
-        if (mode == MODE_JOINT && is_vis(p)) return ordered_key(sv[p - Ns] * vscale);
-        return ordered_key(st[p < Ns ? p : p - Nv]);
+        if (mode == MODE_JOINT && is_vis(p)) x *= vscale;
+        return ordered_key(x);
+    }
+    __device__ uint32_t key(int p) const {
+        return key_of(p, is_vis(p) ? sv[p - Ns] : st[p < Ns ? p : p - Nv]);
     }
     // kept without competing (forced in the text/vision modes, all text in the vision mode)
     __device__ bool kept_outright(int p) const {
@@ -93,22 +104,9 @@ __device__ void find_digit(const int* hist, int kr, uint32_t* sel) {
     }
 }
 
-template <bool LDS_KEYS>
-__global__ __launch_bounds__(kThreads) void select_kernel(Shape s, const float* __restrict__ s_vis,
-                                                          const float* __restrict__ s_txt,
-                                                          const int32_t* __restrict__ budgets,
-                                                          const int64_t* __restrict__ idx_off,
-                                                          int32_t* __restrict__ idx) {
-    __shared__ int hist[256];
-    __shared__ int wtot[kWaves][2];
-    __shared__ uint32_t sel[2];
-    __shared__ uint32_t keys[LDS_KEYS ? kLdsKeys : 1];
-    const int tid = threadIdx.x;
-    const int gi = blockIdx.x % s.ngroups;
-    const int bl = blockIdx.x / s.ngroups;
-    const int bgt = budgets[bl];
-    int32_t* out = idx + idx_off[bl] + (int64_t)gi * bgt;
-
+// The row's layout and mode for its budget; k: how many candidates to take, nc: how many there are.
+__device__ __forceinline__ RowCtx row_ctx(const Shape& s, const float* s_vis, const float* s_txt, int bl, int gi,
+                                          int bgt, int& k, int& nc) {
     RowCtx c;
     c.N = s.N;
     c.Ns = s.Ns;
@@ -125,22 +123,35 @@ __global__ __launch_bounds__(kThreads) void select_kernel(Shape s, const float* 
     const int nf = c.fs + (s.N - c.fr);
     const int ntf = max(0, min(s.Ns, c.fr) - c.fs) + max(0, c.fr - max(s.Ns + s.Nv, c.fs));
 
-    int k;
     if (bgt <= nf) { c.mode = MODE_FORCED; k = bgt; }
     else if (s.joint_rank) { c.mode = MODE_JOINT; k = bgt - nf; }
     else if (bgt - nf <= ntf) { c.mode = MODE_TEXT; k = bgt - nf; }
     else { c.mode = MODE_VIS; k = bgt - nf - ntf; }
-    const int nc = c.mode == MODE_FORCED ? nf
+    nc = c.mode == MODE_FORCED ? nf
                  : c.mode == MODE_JOINT  ? s.N - nf
                  : c.mode == MODE_TEXT   ? ntf
                                          : s.N - nf - ntf;
+    return c;
+}
 
-    // key lookup: from LDS when the row fits (kNotCand marks non-candidates), else re-read
-    auto key_at = [&](int p) -> uint32_t { return LDS_KEYS ? keys[p] : (c.cand(p) ? c.key(p) : kNotCand); };
-    if (LDS_KEYS) {
-        for (int p = tid; p < s.N; p += kThreads) keys[p] = c.cand(p) ? c.key(p) : kNotCand;
-        __syncthreads();
-    }
+__global__ __launch_bounds__(kThreads) void select_long_kernel(Shape s, const float* __restrict__ s_vis,
+                                                          const float* __restrict__ s_txt,
+                                                          const int32_t* __restrict__ budgets,
+                                                          const int64_t* __restrict__ idx_off,
+                                                          int32_t* __restrict__ idx) {
+    __shared__ int hist[256];
+    __shared__ int wtot[kWaves][2];
+    __shared__ uint32_t sel[2];
+    const int tid = threadIdx.x;
+    const int gi = blockIdx.x % s.ngroups;
+    const int bl = blockIdx.x / s.ngroups;
+    const int bgt = budgets[bl];
+    int32_t* out = idx + idx_off[bl] + (int64_t)gi * bgt;
+
+    int k, nc;
+    const RowCtx c = row_ctx(s, s_vis, s_txt, bl, gi, bgt, k, nc);
+
+    auto key_at = [&](int p) -> uint32_t { return c.cand(p) ? c.key(p) : kNotCand; };
 
     uint32_t thr;
     int take_ties;
@@ -218,18 +229,214 @@ __global__ __launch_bounds__(kThreads) void select_kernel(Shape s, const float* 
     }
 }
 
+// The k-th largest of a row whose keys lie in registers: thr its key, take_ties how many keys equal
+// to it are taken (kNotCand marks non-candidates; 0 < k < number of candidates).
+template <int GPW>
+__device__ __forceinline__ void select_threshold(const uint32_t (&key)[GPW], int k, int* hist, uint32_t* list,
+                                                 uint32_t (*wred)[2], uint32_t* sel, uint32_t& thr, int& take_ties) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    // smallest and largest candidate key
+    uint32_t lo = 0xFFFFFFFFu, hi = 0u;
+#pragma unroll
+    for (int i = 0; i < GPW; ++i) {
+        lo = min(lo, key[i] != kNotCand ? key[i] : 0xFFFFFFFFu);
+        hi = max(hi, key[i]);
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        lo = min(lo, shfl_xor(lo, o));
+        hi = max(hi, shfl_xor(hi, o));
+    }
+    if (lane == 0) {
+        wred[wave][0] = lo;
+        wred[wave][1] = hi;
+    }
+    hist[tid] = 0;
+    hist[tid + kThreads] = 0;
+    __syncthreads();
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+        lo = min(lo, wred[w][0]);
+        hi = max(hi, wred[w][1]);
+    }
+    thr = lo;
+    take_ties = k;
+    int top = lo == hi ? 0 : 32 - __clz((int)(lo ^ hi));  // bits still open; the higher ones are settled
+    int kr = k;
+    uint32_t prefix = top >= 32 ? 0u : hi >> top << top;
+    while (top > 0) {  // each pass settles at least one bit
+        const int shift = max(top - kBits, 0);
+        const uint32_t settled = top >= 32 ? 0u : ~0u << top;
+#pragma unroll
+        for (int i = 0; i < GPW; ++i)
+            if (key[i] != kNotCand && (key[i] & settled) == prefix)
+                atomicAdd(&hist[(key[i] >> shift) & (kBins - 1) & ~(settled >> shift)], 1);
+        __syncthreads();
+        // the bin where the count of larger keys reaches kr: thread t holds bins 2047 - 2t and 2046 - 2t
+        const int c0 = hist[kBins - 1 - 2 * tid], c1 = hist[kBins - 2 - 2 * tid];
+        int incl = c0 + c1;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int y = __shfl_up(incl, o, 64);
+            if (lane >= o) incl += y;
+        }
+        if (lane == 63) wred[wave][0] = (uint32_t)incl;
+        __syncthreads();
+        int before = 0;  // keys in the bins of the waves before
+#pragma unroll
+        for (int w = 0; w < kWaves; ++w) before += w < wave ? (int)wred[w][0] : 0;
+        const int above = before + incl - c0 - c1;
+        if (above < kr && above + c0 + c1 >= kr) {
+            const bool first = above + c0 >= kr;
+            sel[0] = (uint32_t)(first ? kBins - 1 - 2 * tid : kBins - 2 - 2 * tid);
+            sel[1] = (uint32_t)(kr - (first ? above : above + c0));
+            sel[2] = (uint32_t)(first ? c0 : c1);
+            sel[3] = 0u;
+        }
+        hist[kBins - 1 - 2 * tid] = 0;
+        hist[kBins - 2 - 2 * tid] = 0;
+        __syncthreads();
+        prefix |= sel[0] << shift;
+        kr = (int)sel[1];
+        const int cnt = (int)sel[2];
+        top = shift;
+        thr = prefix;
+        take_ties = kr;
+        if (top == 0) break;
+        if (cnt <= 64) {  // few keys left: rank them all against all
+            const uint32_t sd = ~0u << top;
+#pragma unroll
+            for (int i = 0; i < GPW; ++i)
+                if (key[i] != kNotCand && (key[i] & sd) == prefix) list[atomicAdd(&sel[3], 1u)] = key[i];
+            __syncthreads();
+            if (wave == 0) {
+                const uint32_t mine = lane < cnt ? list[lane] : 0u;
+                int gt = 0, ge = 0;  // larger, and larger or equal
+                for (int j = 0; j < cnt; ++j) {
+                    const uint32_t o = list[j];
+                    gt += o > mine;
+                    ge += o >= mine;
+                }
+                if (lane < cnt && gt < kr && ge >= kr) {  // every lane holding the k-th key writes the same
+                    sel[0] = mine;
+                    sel[1] = (uint32_t)(kr - gt);
+                }
+            }
+            __syncthreads();
+            thr = sel[0];
+            take_ties = (int)sel[1];
+            break;
+        }
+        __syncthreads();  // sel is rewritten by the next pass
+    }
+}
+
+template <int GPW>
+__global__ __launch_bounds__(kThreads) void select_kernel(Shape s, const float* __restrict__ s_vis,
+                                                          const float* __restrict__ s_txt,
+                                                          const int32_t* __restrict__ budgets,
+                                                          const int64_t* __restrict__ idx_off,
+                                                          int32_t* __restrict__ idx) {
+    __shared__ int hist[kBins];
+    __shared__ uint32_t list[64];
+    __shared__ uint32_t wred[kWaves][2];
+    __shared__ uint32_t sel[4];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int gi = blockIdx.x % s.ngroups;
+    const int bl = blockIdx.x / s.ngroups;
+    const int bgt = budgets[bl];
+    int32_t* out = idx + idx_off[bl] + (int64_t)gi * bgt;
+    // each wave's contiguous run of 64-position groups
+    const int ngrp = (s.N + 63) >> 6;
+    const int gpw = (ngrp + kWaves - 1) / kWaves;  // <= GPW
+    const int g0 = wave * gpw, g1 = min(g0 + gpw, ngrp);
+
+    // every score of the row is fetched at once, whatever the mode will make of it (the text scores
+    // only at text positions, the vision scores only at vision positions; clamped, so each load is issued)
+    const float* sv = s_vis + ((size_t)bl * s.ngroups + gi) * s.Nv;
+    const float* st = s_txt + ((size_t)bl * s.ngroups + gi) * s.Nt;
+    float sc[GPW];
+#pragma unroll
+    for (int i = 0; i < GPW; ++i) {
+        const int p = min((g0 + i) * 64 + lane, s.N - 1);
+        const bool vis = p >= s.Ns && p < s.Ns + s.Nv;
+        sc[i] = *(vis ? sv + (p - s.Ns) : st + (p < s.Ns ? p : p - s.Nv));
+    }
+    int k, nc;
+    const RowCtx c = row_ctx(s, s_vis, s_txt, bl, gi, bgt, k, nc);
+    uint32_t key[GPW];
+    uint32_t outright = 0u;  // bit i: position i of the lane is kept without competing
+#pragma unroll
+    for (int i = 0; i < GPW; ++i) {
+        const int p = (g0 + i) * 64 + lane;
+        key[i] = kNotCand;
+        if (g0 + i < g1 && p < s.N) {
+            if (c.kept_outright(p)) outright |= 1u << i;
+            else if (c.cand(p)) key[i] = c.key_of(p, sc[i]);
+        }
+    }
+
+    uint32_t thr;
+    int take_ties;
+    if (k <= 0) { thr = 0xFFFFFFFFu; take_ties = 0; }
+    else if (k >= nc) { thr = 0u; take_ties = nc; }
+    else select_threshold<GPW>(key, k, hist, list, wred, sel, thr, take_ties);
+
+    // ordered emission (see the header): count, one barrier, rank and write
+    const unsigned long long below = (1ull << lane) - 1ull;
+    int nt = 0, nk = 0;  // the wave's ties and other kept positions
+#pragma unroll
+    for (int i = 0; i < GPW; ++i) {
+        const bool other = (outright >> i & 1u) || (key[i] != kNotCand && key[i] > thr);
+        nt += __popcll(__ballot(key[i] != kNotCand && key[i] == thr));
+        nk += __popcll(__ballot(other));
+    }
+    __syncthreads();  // wred was read by every wave
+    if (lane == 0) {
+        wred[wave][0] = (uint32_t)nt;
+        wred[wave][1] = (uint32_t)nk;
+    }
+    __syncthreads();
+    int tb = 0, ob = 0;  // ties and other kept positions before this wave's run
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) {
+        tb += w < wave ? (int)wred[w][0] : 0;
+        ob += w < wave ? (int)wred[w][1] : 0;
+    }
+#pragma unroll
+    for (int i = 0; i < GPW; ++i) {
+        const bool other = (outright >> i & 1u) || (key[i] != kNotCand && key[i] > thr);
+        const bool tie = key[i] != kNotCand && key[i] == thr;
+        const unsigned long long tm = __ballot(tie);
+        const bool keep = other || (tie && tb + __popcll(tm & below) < take_ties);
+        const unsigned long long km = __ballot(keep);
+        const int pos = ob + min(take_ties, tb) + __popcll(km & below);
+        if (keep && pos < bgt) out[pos] = (g0 + i) * 64 + lane;
+        tb += __popcll(tm);
+        ob += __popcll(__ballot(other));
+    }
+}
+
 }  // namespace
 
 hipError_t launch_select(const Shape& s, const float* s_vis, const float* s_txt, const int32_t* budgets,
                          const int64_t* idx_off, int32_t* idx, hipStream_t st) {
     const long long nblk = (long long)s.B * s.L * s.ngroups;
     if (nblk == 0) return hipSuccess;
-    if (s.N <= kLdsKeys)
-        hipLaunchKernelGGL(select_kernel<true>, dim3((unsigned)nblk), dim3(kThreads), 0, st, s, s_vis, s_txt, budgets,
-                           idx_off, idx);
+    const int gpw = ((s.N + 63) / 64 + kWaves - 1) / kWaves;
+    const dim3 grid((unsigned)nblk), block(kThreads);
+#define TGVKV_SELECT(G) \
+    hipLaunchKernelGGL(select_kernel<G>, grid, block, 0, st, s, s_vis, s_txt, budgets, idx_off, idx)
+    if (gpw <= 1) TGVKV_SELECT(1);
+    else if (gpw <= 2) TGVKV_SELECT(2);
+    else if (gpw <= 3) TGVKV_SELECT(3);
+    else if (gpw <= 4) TGVKV_SELECT(4);
+    else if (gpw <= 6) TGVKV_SELECT(6);
+    else if (gpw <= 9) TGVKV_SELECT(9);
+    else if (gpw <= kRegGroups) TGVKV_SELECT(kRegGroups);
     else
-        hipLaunchKernelGGL(select_kernel<false>, dim3((unsigned)nblk), dim3(kThreads), 0, st, s, s_vis, s_txt,
-                           budgets, idx_off, idx);
+        hipLaunchKernelGGL(select_long_kernel, grid, block, 0, st, s, s_vis, s_txt, budgets, idx_off, idx);
+#undef TGVKV_SELECT
     return hipGetLastError();
 }
 

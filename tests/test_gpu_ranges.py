@@ -5,6 +5,7 @@ Scores use gpu_util's tolerance (2e-3 relative; 32-bit sums are observed near 1e
 import numpy as np
 import pytest
 
+import oracle.tgvkv_oracle as O
 from paper_2606_03075_amd import binding as bd
 from tests.gpu_util import assert_close_rel, dev_bf16, host, log, oracle_scores
 from workloads import make_prefill_tensors
@@ -130,3 +131,40 @@ def test_one_order_in_any_batch(lib):
         assert torch.equal(a[0], b[0]) and torch.equal(b[0], b[78]) and torch.equal(b[1], b[79]), n
     with pytest.raises(bd.TgvkvError):
         one.score(q[:1], k[:1], bd.SCORE_TEXT | bd.SCORE_VISION | bd.SCORE_LSE_IN | bd.SCORE_ONE_ORDER)
+
+
+# positions per row: 64 x 16 waves x 1 to 12 register groups, their neighbours, and rows past the registers
+SELECT_ROWS = [1, 65, 1023, 1024, 1025, 2048, 3073, 4097, 6144, 6145, 9217, 12288, 12289]
+SELECT_VALUES = {
+    "spread": lambda r, n: r.standard_normal(n) * 10.0 ** r.uniform(-30, 30, n),   # the first digit settles little
+    "close": lambda r, n: 1.0 + r.random(n) * 2.0 ** -12,                          # keys differ in the last 11 bits
+    "tied": lambda r, n: r.integers(0, 3, n) - 1.0,                                # -1, 0 and 1: ties in the hundreds
+    "equal": lambda r, n: np.full(n, 0.25),
+    "outlier": lambda r, n: np.where(r.random(n) < 0.01, np.inf, np.where(r.random(n) < 0.01, -np.inf, r.random(n))),
+}
+
+
+@pytest.mark.parametrize("values", sorted(SELECT_VALUES))
+@pytest.mark.parametrize("n", SELECT_ROWS)
+def test_select_rows(lib, n, values):
+    """The k-th largest by radix passes in registers (and, past them, from memory) and the ordered emission, against
+    the oracle: whole numbers, so exact."""
+    import torch
+    log(f"select {n} {values}")
+    r = np.random.default_rng(n)
+    ns, nq = (3, 5) if n > 8 else (0, 0)
+    nv, nt, layers = n - ns - nq, ns + nq, 9
+    sv = SELECT_VALUES[values](r, layers * nv).astype(np.float32).reshape(1, layers, 1, nv)
+    st = SELECT_VALUES[values](r, layers * nt).astype(np.float32).reshape(1, layers, 1, nt)
+    bud = np.clip([0, 1, nt, nt + 1, nt + 2, nt + nv // 17, nt + nv // 2, n - 1, n], 0, n).reshape(1, layers)
+    offsets = O.flat_offsets(bud.reshape(-1))
+    for joint in (False, True):
+        idx = torch.full((max(1, int(offsets[-1])),), -1, dtype=torch.int32, device="cuda")
+        bd.tgvkv_select(bd.make_problem(1, layers, 2, 2, 64, ns, nv, nq), bd.make_opts(vision_rank=1, joint_rank=joint),
+                        torch.from_numpy(sv).cuda(), torch.from_numpy(st).cuda() if nt else torch.zeros(1, device="cuda"),
+                        torch.from_numpy(bud.astype(np.int32)).cuda(), torch.from_numpy(offsets).cuda(), idx)
+        got = host(idx)
+        for l in range(layers):
+            args = (sv[0, l, 0].astype(np.float64), st[0, l, 0].astype(np.float64), int(bud[0, l]), ns, nv, nq)
+            want = O.joint_select(*args, vis_scale=1.0) if joint else O.tpr_select(*args)
+            assert np.array_equal(got[offsets[l]:offsets[l + 1]], want), (l, joint)
