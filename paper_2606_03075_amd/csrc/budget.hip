@@ -34,7 +34,8 @@ constexpr int kThreads = 256;
 template <class Prec, class Emit>
 __device__ void rank_layers(int L, int* part, Prec prec, Emit emit) {
     const int tid = threadIdx.x;
-    const int nch = L <= kThreads / 2 ? kThreads / max(L, 1) : 1;
+    // no more chunks than layers: with one layer, 256 chunks of nothing to add up took 3 of 9.5 us
+    const int nch = L <= kThreads / 2 ? min(kThreads / max(L, 1), L) : 1;
     const int per = (L + nch - 1) / nch;
     for (int t = tid; t < nch * L; t += kThreads) {
         const int l = t % L, c = t / L;
