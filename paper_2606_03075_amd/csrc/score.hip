@@ -721,7 +721,7 @@ hipError_t launch_score_fin(const Shape& s, const float* ws_colsum, const float*
 int vision_splits(const Shape& s, const RowPlan& rp) {
     // With few (unit, row group) workgroups the vision keys are split over several.  Below one round
     // of resident workgroups (3 per CU up to four slots, else 2) the split fills one round, each
-    // share at least 3 key tiles: one video (112 units) in 4 shares 116 us against 125 us in 8
+    // share at least 2 key tiles: one video (112 units) in 4 shares 116 us against 125 us in 8
     // (1.75 rounds); one layer of 128 units 32 -> 24.5 us.  Up to 2048 workgroups two rounds: at the
     // Qwen2-VL shape (896 units, 2 workgroups per CU) two splits balance the last round (805 -> 740
     // us); at 4096 units a split only adds prologues.  The mass-collecting variant writes one row-mass
@@ -732,7 +732,7 @@ int vision_splits(const Shape& s, const RowPlan& rp) {
     const int tiles = (s.Nv + kTile - 1) / kTile;
     if (units * 2 <= round) {
         const int n = (int)std::max<long long>(
-            std::min<long long>(std::min<long long>(round / units, tiles / kMinShareTiles), kMaxShares), 1);
+            std::min<long long>(std::min<long long>(round / units, tiles / 2), kMaxShares), 1);
         const int per = (tiles + n - 1) / n;  // tiles per share; no share is empty
         return per > 0 ? (tiles + per - 1) / per : 1;
     }
