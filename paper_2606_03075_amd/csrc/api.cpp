@@ -142,11 +142,7 @@ ScoreWs score_workspace(const Shape& s, const RowPlan& rp, void* base) {
     return w;
 }
 
-size_t decode_workspace_bytes(const Shape& s) {
-    const int ns = tgvkv::decode_splits(s);
-    if (ns <= 1) return 0;
-    return align_up(sizeof(float) * (size_t)s.B * s.L * s.H * ns * (s.D + 2));
-}
+size_t decode_workspace_bytes(const Shape& s) { return align_up(tgvkv::decode_workspace(s)); }
 
 // Paged cache limits: page_size and max_pages bound the LDS copy of a segment's page ids.
 constexpr int32_t kMaxPageSize = 4096;

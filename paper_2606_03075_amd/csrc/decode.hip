@@ -13,8 +13,8 @@
 //     with every load unconditional, so the compiler's waits stay per block);
 //   * online softmax per lane group, merged across groups with wave shuffles and
 //     across the 4 waves through LDS; when the (sequence, layer, KV head) count is
-//     too small to fill the GPU the token range is split and a second kernel
-//     combines the partial (max, sum, weighted sum) triples.
+//     too small to fill the GPU the token range is split, and the unit's last workgroup to
+//     finish combines the partial (max, sum, weighted sum) triples (combine_splits).
 // The step's new token is read from the k_new / v_new inputs (the cache slot it
 // is written to is not re-read in the same launch).  The cache is either one
 // contiguous segment per (sequence, layer) or fixed-size pages found through a
@@ -23,6 +23,8 @@
 // (from the budget call: longest segments first) sets which (sequence, layer) each
 // workgroup serves, so the long segments do not all start last.
 #include <algorithm>
+#include <atomic>
+#include <chrono>
 #include <climits>
 #include <mutex>
 
@@ -36,6 +38,7 @@ namespace {
 constexpr int kThreads = 256;
 // query heads per KV head from which decode runs on the matrix cores
 constexpr int kMfmaMinGroup = 3;
+constexpr int kMaxSplits = 8;  // of a unit's token range
 
 __device__ __forceinline__ void unpack8(u32x4 r, float (&f)[8]) {
 #pragma unroll
@@ -45,7 +48,95 @@ __device__ __forceinline__ void unpack8(u32x4 r, float (&f)[8]) {
     }
 }
 
-template <int D, int GMAX, class Rows>
+// Split partials in one launch: every workgroup of a unit writes its partial, then its mark, then reads
+// the unit's marks; one that finds them all combines the partials, in split order, and clears the
+// marks.  The workgroup whose mark lands last finds them all, unless another has combined already; two
+// that both find them all write the same values.  No workgroup waits for another.  A launch of its own
+// for the combination cost 5.4 us of kernel and a gap: one layer of 8 sequences (32 units in 8 splits)
+// 14.0 -> 12.3 us per step replayed from a graph, 14.7 -> 11.6 us launched; 32 units of 300 rows, one
+// query head each, 14.4 -> 7.7 us.
+//
+// The marks live in the caller's workspace, whose first contents are unknown, so a mark is the number
+// of its call, 64 bits that differ between calls (counted from a scrambled clock).  A replayed graph
+// brings the same number again, but the last call on a workspace left its marks cleared.
+struct Arrivals {
+    unsigned long long* marks;  // [B*L*H_kv][splits], null without a split
+    unsigned long long call;    // never 0
+};
+
+// Partials pass between workgroups of different XCDs, whose L2 caches are apart.  They are written and
+// read as GPU-scope atomics, which go through to memory, so a finished store (vmcnt) is visible to the
+// whole GPU and no cache has to be written back or dropped: with plain stores and a GPU-scope fence
+// on either side, whose write-back covers the whole L2, the step took 48 us.
+__device__ __forceinline__ void store_shared(float* p, float v) {
+    __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ float load_shared(const float* p) {
+    return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Called by all threads of a workgroup after they wrote its partial of query heads bh0 .. bh0 + G - 1
+// (G <= GMAX).
+template <int D, int GMAX>
+__device__ __forceinline__ void combine_splits(const Arrivals& arr, size_t slot, int split, size_t bh0, int G, int nsplit,
+                                               const float* ws_part, float* __restrict__ out) {
+    constexpr int ITERS = (GMAX * D + kThreads - 1) / kThreads;
+    __shared__ int last;
+    __shared__ float ml[2][GMAX][kMaxSplits];
+    wait_vmem_all();  // this thread's part of the partial has reached memory (store_shared) ...
+    __syncthreads();  // ... and every thread's has, before the arrival
+    unsigned long long* marks = arr.marks + slot * nsplit;
+    if (threadIdx.x < 64) {
+        if (threadIdx.x == 0)
+            __hip_atomic_store(marks + split, arr.call, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        wait_vmem_all();  // the mark has reached memory before the others' are read
+        const bool here = threadIdx.x >= nsplit ||
+                          __hip_atomic_load(marks + threadIdx.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == arr.call;
+        const bool all = __ballot(!here) == 0;
+        if (threadIdx.x == 0) last = all;
+    }
+    __syncthreads();
+    if (!last) return;
+    // every load in flight at once: the weighted sums to registers, maxima and sums to LDS
+    float a[ITERS][kMaxSplits];
+#pragma unroll
+    for (int it = 0; it < ITERS; ++it) {
+        const int x = min((int)threadIdx.x + it * kThreads, G * D - 1);
+        const float* p = ws_part + (bh0 + x / D) * nsplit * (size_t)(D + 2) + 2 + x % D;
+#pragma unroll
+        for (int i = 0; i < kMaxSplits; ++i) a[it][i] = load_shared(p + min(i, nsplit - 1) * (D + 2));
+    }
+    if (threadIdx.x < G * nsplit) {
+        const int h = threadIdx.x / nsplit, i = threadIdx.x % nsplit;
+        const float* p = ws_part + ((bh0 + h) * nsplit + i) * (size_t)(D + 2);
+        const float m = load_shared(p), l = load_shared(p + 1);
+        ml[0][h][i] = m;
+        ml[1][h][i] = l;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int it = 0; it < ITERS; ++it) {
+        const int x = threadIdx.x + it * kThreads;
+        if (x >= G * D) break;
+        const int h = x / D;
+        float M = kNegInf;
+        for (int i = 0; i < nsplit; ++i) M = fmaxf(M, ml[0][h][i]);
+        float num = 0.f, den = 0.f;
+#pragma unroll
+        for (int i = 0; i < kMaxSplits; ++i) {
+            if (i < nsplit) {
+                const float sc = fast_exp2(ml[0][h][i] - M);
+                num += sc * a[it][i];
+                den += sc * ml[1][h][i];
+            }
+        }
+        out[(bh0 + h) * D + x % D] = num / den;
+    }
+    if (threadIdx.x < nsplit)
+        __hip_atomic_store(marks + threadIdx.x, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+template <int D, int GMAX, class Rows, bool SPLIT>
 __global__ __launch_bounds__(kThreads) void decode_kernel(Shape s, Rows rows, uint16_t* __restrict__ kc,
                                                           uint16_t* __restrict__ vc,
                                                           const int32_t* __restrict__ budgets, int reserve, int step,
@@ -53,8 +144,9 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(Shape s, Rows rows, ui
                                                           const uint16_t* __restrict__ q,
                                                           const uint16_t* __restrict__ k_new,
                                                           const uint16_t* __restrict__ v_new, float* __restrict__ out,
-                                                          float* __restrict__ ws_part, int nsplit,
+                                                          float* ws_part, int splits, Arrivals arr,
                                                           const int32_t* __restrict__ unit_order) {
+    const int nsplit = SPLIT ? splits : 1;
     constexpr int LPR = D / 8;         // lanes per token row
     constexpr int GPW = 64 / LPR;      // lane groups per wave
     constexpr int NGRP = 4 * GPW;      // lane groups per workgroup
@@ -231,17 +323,19 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(Shape s, Rows rows, ui
             }
         }
         const size_t bh = (size_t)bl * s.H + kvh * G + h;
-        if (nsplit == 1) {
+        if (!SPLIT) {
             out[bh * D + dd] = num / den;
         } else {
             float* p = ws_part + (bh * nsplit + split) * (size_t)(D + 2);
-            p[2 + dd] = num;
+            store_shared(p + 2 + dd, num);
             if (dd == 0) {
-                p[0] = M;
-                p[1] = den;
+                store_shared(p, M);
+                store_shared(p + 1, den);
             }
         }
     }
+    if constexpr (SPLIT)
+        combine_splits<D, GMAX>(arr, blockIdx.x / nsplit, split, (size_t)bl * s.H + kvh * G, G, nsplit, ws_part, out);
 }
 
 // Grouped-query decode on the matrix cores, for several query heads per KV head.
@@ -270,7 +364,7 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(Shape s, Rows rows, ui
 //     end), so they stream in during the block's softmax and P V.  That keeps the
 //     kernel at 122 VGPRs, 4 waves per SIMD; a second buffer cost a wave per SIMD
 //     and measured slower.  The waves then merge through LDS as the VALU kernel does.
-template <int D, int GMAX, class Rows>
+template <int D, int GMAX, class Rows, bool SPLIT>
 __global__ __launch_bounds__(kThreads) void decode_mfma_kernel(Shape s, Rows rows, uint16_t* __restrict__ kc,
                                                                uint16_t* __restrict__ vc,
                                                                const int32_t* __restrict__ budgets, int reserve,
@@ -278,8 +372,10 @@ __global__ __launch_bounds__(kThreads) void decode_mfma_kernel(Shape s, Rows row
                                                                const uint16_t* __restrict__ q,
                                                                const uint16_t* __restrict__ k_new,
                                                                const uint16_t* __restrict__ v_new,
-                                                               float* __restrict__ out, float* __restrict__ ws_part,
-                                                               int nsplit, const int32_t* __restrict__ unit_order) {
+                                                               float* __restrict__ out, float* ws_part, int splits,
+                                                               Arrivals arr,
+                                                               const int32_t* __restrict__ unit_order) {
+    const int nsplit = SPLIT ? splits : 1;
     constexpr int KSTEPS = D / 32;          // k-steps of S^T = K Q^T over the head dim
     constexpr int NB2 = D / 32;             // pairs of 16-dim output blocks
     constexpr int VROWB = D * 2 + 16;       // padded LDS row of the V stage, bytes
@@ -468,39 +564,34 @@ __global__ __launch_bounds__(kThreads) void decode_mfma_kernel(Shape s, Rows row
             }
         }
         const size_t bh = (size_t)bl * s.H + kvh * G + h;
-        if (nsplit == 1) {
+        if (!SPLIT) {
             out[bh * D + dd] = num / den;
         } else {
             float* p = ws_part + (bh * nsplit + split) * (size_t)(D + 2);
-            p[2 + dd] = num;
+            store_shared(p + 2 + dd, num);
             if (dd == 0) {
-                p[0] = M;
-                p[1] = den;
+                store_shared(p, M);
+                store_shared(p + 1, den);
             }
         }
     }
+    if constexpr (SPLIT)
+        combine_splits<D, GMAX>(arr, blockIdx.x / nsplit, split, (size_t)bl * s.H + kvh * G, G, nsplit, ws_part, out);
 }
 
-template <int D>
-__global__ __launch_bounds__(D) void decode_combine_kernel(Shape s, const float* __restrict__ ws_part, int nsplit,
-                                                           float* __restrict__ out, const int32_t* __restrict__ steps,
-                                                           int reserve) {
-    const size_t bh = blockIdx.x;
-    if (steps != nullptr) {
-        const int st = steps[(int)(bh / ((size_t)s.L * s.H))];
-        if (st < 0 || st >= reserve) return;  // this sequence is not decoding
-    }
-    const int dd = threadIdx.x;
-    const float* p = ws_part + bh * nsplit * (size_t)(D + 2);
-    float M = kNegInf;
-    for (int i = 0; i < nsplit; ++i) M = fmaxf(M, p[i * (D + 2)]);
-    float num = 0.f, den = 0.f;
-    for (int i = 0; i < nsplit; ++i) {
-        const float sc = fast_exp2(p[i * (D + 2)] - M);
-        num += sc * p[i * (D + 2) + 2 + dd];
-        den += sc * p[i * (D + 2) + 1];
-    }
-    out[bh * D + dd] = num / den;
+size_t partial_floats(const Shape& s, int nsplit) {
+    return nsplit > 1 ? (size_t)s.B * s.L * s.H * nsplit * (s.D + 2) : 0;
+}
+
+// The call's marks (behind the partials, 8-byte aligned) and its number.
+Arrivals arrivals(const Shape& s, float* ws_part, int nsplit) {
+    if (nsplit <= 1) return Arrivals{nullptr, 0};
+    static std::atomic<unsigned long long> next{
+        (unsigned long long)std::chrono::steady_clock::now().time_since_epoch().count() * 0x9E3779B97F4A7C15ull};
+    unsigned long long call;
+    do call = next.fetch_add(1, std::memory_order_relaxed); while (call == 0);
+    const uintptr_t end = reinterpret_cast<uintptr_t>(ws_part + partial_floats(s, nsplit));
+    return Arrivals{reinterpret_cast<unsigned long long*>((end + 7) / 8 * 8), call};
 }
 
 template <int D, class Rows>
@@ -509,27 +600,24 @@ hipError_t launch_decode_d(const Shape& s, const Rows& rows, size_t lds_bytes, u
                            const uint16_t* q, const uint16_t* k_new, const uint16_t* v_new, float* out, float* ws_part,
                            int nsplit, const int32_t* unit_order, hipStream_t st) {
     dim3 grid((unsigned)((long long)s.B * s.L * s.Hkv * nsplit)), block(kThreads);
-#define TGVKV_DECODE_LAUNCH(GM)                                                                                   \
-    hipLaunchKernelGGL((decode_kernel<D, GM, Rows>), grid, block, lds_bytes, st, s, rows, kc, vc, budgets, reserve, \
-                       step, steps, q, k_new, v_new, out, ws_part, nsplit, unit_order)
-#define TGVKV_DECODE_MFMA_LAUNCH(GM)                                                                           \
-    hipLaunchKernelGGL((decode_mfma_kernel<D, GM, Rows>), grid, block, lds_bytes, st, s, rows, kc, vc, budgets,     \
-                       reserve, step, steps, q, k_new, v_new, out, ws_part, nsplit, unit_order)
-    if (s.G >= kMfmaMinGroup) {
-        if (s.G <= 4) TGVKV_DECODE_MFMA_LAUNCH(4);
-        else if (s.G <= 8) TGVKV_DECODE_MFMA_LAUNCH(8);
-        else TGVKV_DECODE_MFMA_LAUNCH(16);
-    } else if (s.G <= 1) TGVKV_DECODE_LAUNCH(1);
-    else if (s.G <= 2) TGVKV_DECODE_LAUNCH(2);
-    else if (s.G <= 4) TGVKV_DECODE_LAUNCH(4);
-    else if (s.G <= 8) TGVKV_DECODE_LAUNCH(8);
-    else TGVKV_DECODE_LAUNCH(16);
-#undef TGVKV_DECODE_LAUNCH
-#undef TGVKV_DECODE_MFMA_LAUNCH
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess || nsplit == 1) return e;
-    hipLaunchKernelGGL(decode_combine_kernel<D>, dim3((unsigned)((long long)s.B * s.L * s.H)), dim3(D), 0, st, s,
-                       ws_part, nsplit, out, steps, reserve);
+    const Arrivals arr = arrivals(s, ws_part, nsplit);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, block, lds_bytes, st, s, rows, kc, vc, budgets, reserve, step, steps, q, k_new,
+                           v_new, out, ws_part, nsplit, arr, unit_order);
+    };
+    if (nsplit > 1) {
+        if (s.G <= 1) launch(decode_kernel<D, 1, Rows, true>);
+        else if (s.G < kMfmaMinGroup) launch(decode_kernel<D, 2, Rows, true>);
+        else if (s.G <= 4) launch(decode_mfma_kernel<D, 4, Rows, true>);
+        else if (s.G <= 8) launch(decode_mfma_kernel<D, 8, Rows, true>);
+        else launch(decode_mfma_kernel<D, 16, Rows, true>);
+    } else {
+        if (s.G <= 1) launch(decode_kernel<D, 1, Rows, false>);
+        else if (s.G < kMfmaMinGroup) launch(decode_kernel<D, 2, Rows, false>);
+        else if (s.G <= 4) launch(decode_mfma_kernel<D, 4, Rows, false>);
+        else if (s.G <= 8) launch(decode_mfma_kernel<D, 8, Rows, false>);
+        else launch(decode_mfma_kernel<D, 16, Rows, false>);
+    }
     return hipGetLastError();
 }
 
@@ -563,14 +651,21 @@ hipError_t decode_scratch(float** ptr) {
 int decode_splits(const Shape& s) {
     const long long units = (long long)s.B * s.L * s.Hkv;
     if (units <= 0) return 1;
-    // split a unit's tokens only up to about 1024 workgroups (one round of 4 workgroups per
-    // CU): a split costs partial writes and the combine launch (at the Qwen2-VL shape, 896
-    // units: 40.8 us unsplit against 46.3 us in two splits; at the LLaVA-1.5 shape, 1024 units
-    // at 5 %: 10.0 us per step replayed from a HIP graph unsplit against 17.2 us in two splits)
-    long long n = 1024 / units;
+    // split a unit's tokens only while the workgroups fit one per CU: a partial costs its trip
+    // through memory and the combination about 4 us at the end, and one workgroup's waves already keep
+    // a CU's share of the stream in flight.  Against splitting up to 1024 workgroups (4 per CU), per
+    // step: 128 units of 300 rows 9.9 against 12.1 us, 256 units of 300 rows 10.2 against 13.5, 112
+    // units of 830 rows 15.9 against 19.2 and of 4200 rows 43.5 against 50.0, 512 units of 440 rows
+    // 22.2 against 26.3; at 32 units (8 splits either way) 11.7.
+    long long n = 256 / units;
     if (n < 1) n = 1;
-    if (n > 8) n = 8;
+    if (n > kMaxSplits) n = kMaxSplits;
     return (int)n;
+}
+
+size_t decode_workspace(const Shape& s) {
+    const int n = decode_splits(s);
+    return n <= 1 ? 0 : sizeof(float) * partial_floats(s, n) + 8 + sizeof(unsigned long long) * (size_t)s.B * s.L * s.Hkv * n;
 }
 
 hipError_t launch_decode(const Shape& s, uint16_t* kc, uint16_t* vc, const int32_t* budgets, const int64_t* seg_off,

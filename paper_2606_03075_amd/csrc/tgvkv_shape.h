@@ -78,6 +78,8 @@ hipError_t launch_compact_paged(const Shape& s, const uint16_t* k, const uint16_
                                 const int32_t* unit_order, uint16_t* k_pool, uint16_t* v_pool, hipStream_t st);
 
 int decode_splits(const Shape& s);
+// Bytes of decode's workspace: the split partials and their marks (0 without a split).
+size_t decode_workspace(const Shape& s);
 // Bytes of the per-GPU static buffer that holds decode's split partials for callers that
 // cannot allocate, and its device address on the current device (looked up once per device).
 constexpr size_t kDecodeScratchBytes = size_t(16) << 20;

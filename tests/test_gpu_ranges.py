@@ -168,3 +168,44 @@ def test_select_rows(lib, n, values):
             args = (sv[0, l, 0].astype(np.float64), st[0, l, 0].astype(np.float64), int(bud[0, l]), ns, nv, nq)
             want = O.joint_select(*args, vis_scale=1.0) if joint else O.tpr_select(*args)
             assert np.array_equal(got[offsets[l]:offsets[l + 1]], want), (l, joint)
+
+
+@pytest.mark.parametrize("heads_q,heads_kv,head_dim", [(2, 2, 128), (4, 2, 64), (8, 2, 128), (14, 2, 128), (16, 1, 64)])
+@pytest.mark.parametrize("segments", [1, 9, 16, 43, 64, 65, 128, 129])
+def test_split_decode(lib, segments, heads_q, heads_kv, head_dim):
+    """Decode around the unit counts where a unit's tokens are split (up to 256 units), its partials combined by the
+    unit's last workgroup: any first contents of the workspace, and call after call on the same workspace.
+
+    Outputs are means of values near 1 under probabilities of 16 bits or more: within 1e-4 of 64 bits."""
+    import torch
+    log(f"split decode {segments} segments {heads_q}/{heads_kv} d{head_dim}")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(segments)
+    r = np.random.default_rng(segments)
+    reserve, steps = 3, 3
+    bud = r.integers(0, 200, segments).astype(np.int32)
+    bud[0] = 0
+    p = bd.make_problem(1, segments, heads_q, heads_kv, head_dim, 4, 300, 8)
+    seg = np.concatenate([[0], np.cumsum(bud.astype(np.int64) + reserve)])
+    cache = [torch.randn(int(seg[-1]) * heads_kv * head_dim, generator=g, device="cuda", dtype=torch.bfloat16)
+             for _ in range(2)]
+    need = bd.workspace_size(p, None, bd.CALL_DECODE)
+    assert (need > 0) == (segments * heads_kv <= 128)
+    out = torch.empty(1, segments, heads_q, head_dim, device="cuda")
+    for fill in ("random", "ones"):
+        ws = torch.randint(0, 256, (max(need, 1),), generator=g, device="cuda", dtype=torch.uint8)
+        if fill == "ones":
+            ws.fill_(255)
+        for step in range(steps):
+            q, kn, vn = (torch.randn(1, segments, h, head_dim, generator=g, device="cuda", dtype=torch.bfloat16)
+                         for h in (heads_q, heads_kv, heads_kv))
+            bd.tgvkv_decode_attn(p, None, *cache, torch.from_numpy(bud).cuda(), torch.from_numpy(seg).cuda(), reserve,
+                                 step, q, kn, vn, out, ws)
+            for l in range(segments):
+                n, cap = int(bud[l]) + step + 1, int(bud[l]) + reserve
+                k, v = (c[seg[l] * heads_kv * head_dim:seg[l + 1] * heads_kv * head_dim].view(heads_kv, cap, head_dim)
+                        [:, :n].double() for c in cache)
+                assert torch.equal(k[:, -1], kn[0, l].double())
+                z = torch.matmul(q[0, l].double().view(heads_kv, -1, head_dim), k.transpose(1, 2).contiguous())
+                want = torch.matmul(torch.softmax(z / head_dim ** 0.5, -1), v).view(heads_q, head_dim)
+                assert (out[0, l].double() - want).abs().max().item() <= 1e-4, (fill, step, l)
