@@ -9,31 +9,31 @@
 // ascending order, with no sort: each wave takes a contiguous run of 64-position
 // groups, wave ballots count and rank the ties and the kept positions, and the waves'
 // counts, added across one barrier, give each run the rank of its first tie and the
-// output slot of its first kept position.  The workgroup has 1024 threads: the work is
-// a few latency-bound rounds per (sequence, layer, group), and there are few such units.
+// output slot of its first kept position.  The work is a few latency-bound rounds per
+// (sequence, layer, group), and there are few such units, so long rows get 1024 threads.
 // Without TPR (an ablation of Table 5) all non-forced positions compete on one scale:
 // text by s^T, vision by s^V times a factor (N_t under TWR, whose weights sum to 1).
 //
-// Rows up to kRegRow positions keep their keys in registers, in the emission's layout (a lane's
+// Rows up to 12288 positions keep their keys in registers, in the emission's layout (a lane's
 // keys are its positions of the wave's groups): each score is read once, with every load of the
 // row in flight, and neither the select's passes nor the emission touch memory again.  The select
-// starts at the highest bit in which the row's keys differ and takes 11 bits a pass, so scores of
+// starts at the highest bit in which the row's keys differ and takes 9 to 11 bits a pass, so scores of
 // similar size spread over the bins at once (an 8-bit pass from the top puts nearly all of them in one
 // or two bins, whose LDS atomics then serialise); once at most 64 keys share the k-th key's
 // digits, one wave ranks them all against all.  Longer rows re-read the scores in four 8-bit
-// passes.  8256 positions, 224 rows: 28.6 -> 17.2 us; 2979 positions, 128 rows: 13.8 -> 9.1 us;
-// 651 positions, 32 rows: 7.5 -> 6.4 us (kernel trace).
+// passes.  8256 positions, 224 rows: 25.2 -> 16.2 us; 2979 positions, 128 rows: 12.7 -> 8.3 us;
+// 651 positions, 32 rows: 6.5 -> 5.3 us (replayed from a graph).
 #include "tgvkv_device.h"
 #include "tgvkv_shape.h"
 
 namespace tgvkv {
 namespace {
 
-constexpr int kThreads = 1024;
+constexpr int kThreads = 1024;  // of the kernel for long rows
 constexpr int kWaves = kThreads / 64;
-constexpr int kRegGroups = 12;                       // 64-position groups per wave kept in registers
-constexpr int kRegRow = kRegGroups * kThreads;       // 12288 positions
-constexpr int kBits = 11, kBins = 1 << kBits;        // digits of the register select
+constexpr int kRegGroups = 12;  // most 64-position groups per wave kept in registers: 12288 positions by 16 waves
+// Digits of the register select: two bins a thread.
+constexpr int digit_bits(int waves) { return waves >= 16 ? 11 : waves >= 8 ? 10 : 9; }
 enum { MODE_FORCED = 0, MODE_TEXT = 1, MODE_VIS = 2, MODE_JOINT = 3 };
 constexpr uint32_t kNotCand = 0u;  // keys of real candidates have the top bit or are >= 1
 
@@ -231,9 +231,11 @@ __global__ __launch_bounds__(kThreads) void select_long_kernel(Shape s, const fl
 
 // The k-th largest of a row whose keys lie in registers: thr its key, take_ties how many keys equal
 // to it are taken (kNotCand marks non-candidates; 0 < k < number of candidates).
-template <int GPW>
+template <int WAVES, int GPW>
 __device__ __forceinline__ void select_threshold(const uint32_t (&key)[GPW], int k, int* hist, uint32_t* list,
                                                  uint32_t (*wred)[2], uint32_t* sel, uint32_t& thr, int& take_ties) {
+    constexpr int THREADS = 64 * WAVES, BITS = digit_bits(WAVES), BINS = 1 << BITS;
+    static_assert(BINS == 2 * THREADS, "two bins a thread");
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     // smallest and largest candidate key
     uint32_t lo = 0xFFFFFFFFu, hi = 0u;
@@ -252,10 +254,10 @@ __device__ __forceinline__ void select_threshold(const uint32_t (&key)[GPW], int
         wred[wave][1] = hi;
     }
     hist[tid] = 0;
-    hist[tid + kThreads] = 0;
+    hist[tid + THREADS] = 0;
     __syncthreads();
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
+    for (int w = 0; w < WAVES; ++w) {
         lo = min(lo, wred[w][0]);
         hi = max(hi, wred[w][1]);
     }
@@ -265,15 +267,15 @@ __device__ __forceinline__ void select_threshold(const uint32_t (&key)[GPW], int
     int kr = k;
     uint32_t prefix = top >= 32 ? 0u : hi >> top << top;
     while (top > 0) {  // each pass settles at least one bit
-        const int shift = max(top - kBits, 0);
+        const int shift = max(top - BITS, 0);
         const uint32_t settled = top >= 32 ? 0u : ~0u << top;
 #pragma unroll
         for (int i = 0; i < GPW; ++i)
             if (key[i] != kNotCand && (key[i] & settled) == prefix)
-                atomicAdd(&hist[(key[i] >> shift) & (kBins - 1) & ~(settled >> shift)], 1);
+                atomicAdd(&hist[(key[i] >> shift) & (BINS - 1) & ~(settled >> shift)], 1);
         __syncthreads();
-        // the bin where the count of larger keys reaches kr: thread t holds bins 2047 - 2t and 2046 - 2t
-        const int c0 = hist[kBins - 1 - 2 * tid], c1 = hist[kBins - 2 - 2 * tid];
+        // the bin where the count of larger keys reaches kr: thread t holds the bins 2t and 2t + 1 from the top
+        const int c0 = hist[BINS - 1 - 2 * tid], c1 = hist[BINS - 2 - 2 * tid];
         int incl = c0 + c1;
 #pragma unroll
         for (int o = 1; o < 64; o <<= 1) {
@@ -284,17 +286,17 @@ __device__ __forceinline__ void select_threshold(const uint32_t (&key)[GPW], int
         __syncthreads();
         int before = 0;  // keys in the bins of the waves before
 #pragma unroll
-        for (int w = 0; w < kWaves; ++w) before += w < wave ? (int)wred[w][0] : 0;
+        for (int w = 0; w < WAVES; ++w) before += w < wave ? (int)wred[w][0] : 0;
         const int above = before + incl - c0 - c1;
         if (above < kr && above + c0 + c1 >= kr) {
             const bool first = above + c0 >= kr;
-            sel[0] = (uint32_t)(first ? kBins - 1 - 2 * tid : kBins - 2 - 2 * tid);
+            sel[0] = (uint32_t)(first ? BINS - 1 - 2 * tid : BINS - 2 - 2 * tid);
             sel[1] = (uint32_t)(kr - (first ? above : above + c0));
             sel[2] = (uint32_t)(first ? c0 : c1);
             sel[3] = 0u;
         }
-        hist[kBins - 1 - 2 * tid] = 0;
-        hist[kBins - 2 - 2 * tid] = 0;
+        hist[BINS - 1 - 2 * tid] = 0;
+        hist[BINS - 2 - 2 * tid] = 0;
         __syncthreads();
         prefix |= sel[0] << shift;
         kr = (int)sel[1];
@@ -331,15 +333,15 @@ __device__ __forceinline__ void select_threshold(const uint32_t (&key)[GPW], int
     }
 }
 
-template <int GPW>
-__global__ __launch_bounds__(kThreads) void select_kernel(Shape s, const float* __restrict__ s_vis,
+template <int WAVES, int GPW>
+__global__ __launch_bounds__(64 * WAVES) void select_kernel(Shape s, const float* __restrict__ s_vis,
                                                           const float* __restrict__ s_txt,
                                                           const int32_t* __restrict__ budgets,
                                                           const int64_t* __restrict__ idx_off,
                                                           int32_t* __restrict__ idx) {
-    __shared__ int hist[kBins];
+    __shared__ int hist[2 * 64 * WAVES];
     __shared__ uint32_t list[64];
-    __shared__ uint32_t wred[kWaves][2];
+    __shared__ uint32_t wred[WAVES][2];
     __shared__ uint32_t sel[4];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int gi = blockIdx.x % s.ngroups;
@@ -348,7 +350,7 @@ __global__ __launch_bounds__(kThreads) void select_kernel(Shape s, const float* 
     int32_t* out = idx + idx_off[bl] + (int64_t)gi * bgt;
     // each wave's contiguous run of 64-position groups
     const int ngrp = (s.N + 63) >> 6;
-    const int gpw = (ngrp + kWaves - 1) / kWaves;  // <= GPW
+    const int gpw = (ngrp + WAVES - 1) / WAVES;  // <= GPW
     const int g0 = wave * gpw, g1 = min(g0 + gpw, ngrp);
 
     // every score of the row is fetched at once, whatever the mode will make of it (the text scores
@@ -380,7 +382,7 @@ __global__ __launch_bounds__(kThreads) void select_kernel(Shape s, const float* 
     int take_ties;
     if (k <= 0) { thr = 0xFFFFFFFFu; take_ties = 0; }
     else if (k >= nc) { thr = 0u; take_ties = nc; }
-    else select_threshold<GPW>(key, k, hist, list, wred, sel, thr, take_ties);
+    else select_threshold<WAVES, GPW>(key, k, hist, list, wred, sel, thr, take_ties);
 
     // ordered emission (see the header): count, one barrier, rank and write
     const unsigned long long below = (1ull << lane) - 1ull;
@@ -399,7 +401,7 @@ __global__ __launch_bounds__(kThreads) void select_kernel(Shape s, const float* 
     __syncthreads();
     int tb = 0, ob = 0;  // ties and other kept positions before this wave's run
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
+    for (int w = 0; w < WAVES; ++w) {
         tb += w < wave ? (int)wred[w][0] : 0;
         ob += w < wave ? (int)wred[w][1] : 0;
     }
@@ -423,20 +425,26 @@ hipError_t launch_select(const Shape& s, const float* s_vis, const float* s_txt,
                          const int64_t* idx_off, int32_t* idx, hipStream_t st) {
     const long long nblk = (long long)s.B * s.L * s.ngroups;
     if (nblk == 0) return hipSuccess;
-    const int gpw = ((s.N + 63) / 64 + kWaves - 1) / kWaves;
-    const dim3 grid((unsigned)nblk), block(kThreads);
-#define TGVKV_SELECT(G) \
-    hipLaunchKernelGGL(select_kernel<G>, grid, block, 0, st, s, s_vis, s_txt, budgets, idx_off, idx)
-    if (gpw <= 1) TGVKV_SELECT(1);
-    else if (gpw <= 2) TGVKV_SELECT(2);
-    else if (gpw <= 3) TGVKV_SELECT(3);
-    else if (gpw <= 4) TGVKV_SELECT(4);
-    else if (gpw <= 6) TGVKV_SELECT(6);
-    else if (gpw <= 9) TGVKV_SELECT(9);
-    else if (gpw <= kRegGroups) TGVKV_SELECT(kRegGroups);
-    else
-        hipLaunchKernelGGL(select_long_kernel, grid, block, 0, st, s, s_vis, s_txt, budgets, idx_off, idx);
-#undef TGVKV_SELECT
+    const int groups = (s.N + 63) / 64;
+    const dim3 grid((unsigned)nblk);
+    auto launch = [&](auto kernel, int waves) {
+        hipLaunchKernelGGL(kernel, grid, dim3(64 * waves), 0, st, s, s_vis, s_txt, budgets, idx_off, idx);
+    };
+    // 4 waves up to 768 positions, 8 up to 3072, else 16: fewer waves meet at their barriers sooner and
+    // more rows share a CU, more waves hold longer rows.  1 row of 168 positions 3.9 us (16 waves
+    // 5.5); 490 rows of 558 7.1 (9.1); 128 rows of 999 6.1 by 4 waves, 5.6 by 8, 6.5 by 16; of 2979 10.7,
+    // 8.3, 8.9; 224 rows of 4064 12.2 by 8, 10.5 by 16 (replayed from a graph).
+    if (groups <= 4) launch(select_kernel<4, 1>, 4);
+    else if (groups <= 8) launch(select_kernel<4, 2>, 4);
+    else if (groups <= 12) launch(select_kernel<4, 3>, 4);
+    else if (groups <= 16) launch(select_kernel<8, 2>, 8);
+    else if (groups <= 24) launch(select_kernel<8, 3>, 8);
+    else if (groups <= 48) launch(select_kernel<8, 6>, 8);
+    else if (groups <= 64) launch(select_kernel<16, 4>, 16);
+    else if (groups <= 96) launch(select_kernel<16, 6>, 16);
+    else if (groups <= 144) launch(select_kernel<16, 9>, 16);
+    else if (groups <= 16 * kRegGroups) launch(select_kernel<16, kRegGroups>, 16);
+    else launch(select_long_kernel, kWaves);
     return hipGetLastError();
 }
 

@@ -133,8 +133,8 @@ def test_one_order_in_any_batch(lib):
         one.score(q[:1], k[:1], bd.SCORE_TEXT | bd.SCORE_VISION | bd.SCORE_LSE_IN | bd.SCORE_ONE_ORDER)
 
 
-# positions per row: 64 x 16 waves x 1 to 12 register groups, their neighbours, and rows past the registers
-SELECT_ROWS = [1, 65, 1023, 1024, 1025, 2048, 3073, 4097, 6144, 6145, 9217, 12288, 12289]
+# positions per row: each count of waves and register groups to its last position, the first past it, and past them all
+SELECT_ROWS = [1, 65, 256, 257, 512, 768, 769, 1024, 1025, 1536, 3072, 3073, 4096, 4097, 6144, 9216, 9217, 12288, 12289]
 SELECT_VALUES = {
     "spread": lambda r, n: r.standard_normal(n) * 10.0 ** r.uniform(-30, 30, n),   # the first digit settles little
     "close": lambda r, n: 1.0 + r.random(n) * 2.0 ** -12,                          # keys differ in the last 11 bits
