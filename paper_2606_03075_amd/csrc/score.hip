@@ -590,13 +590,21 @@ RowPlan plan_question_rows(const Shape& s, bool one_order) {
 // about 50 against 21; 16 units of 336 rows, 464 keys 41.7 against 28.3.  112 units of 336 rows
 // over 8256 keys: 288 us whole, 124 split.  Shares of 3 tiles against 4: 17.3 against 20.9 us in
 // the sweep at 4 units, 1-2 us shorter at 32.
+// With one or two row slots a sweep is a stream of keys and a workgroup on every second CU already
+// draws much of the bandwidth, so it is split up to 128 units only, and the more units the longer
+// they have to be: 128 units of 2979 keys 47.6 us whole against 37.0 split, of 1221 keys 21.2 against
+// 23.3, 64 units of 1221 keys 20.9 against 19.6; 256 units of 1221 keys 25.0 us
+// whole against 31.1 split, 480 units of 2979 keys 76.6 against 82.4 (six slots: 224 units of 1583
+// keys 92.5 against 75.9, 4078 keys 127.7 against 108.0).
 constexpr int kMinShareTiles = 3;
 constexpr int kMaxShares = 32;
+constexpr int kLightUnits = 128;
 
 int stats_splits(const Shape& s, const RowPlan& rp) {
     const long long units = (long long)s.B * s.L * s.Hkv * rp.rowgroups;
     const int tiles = (s.N + kTile - 1) / kTile;
     if (rp.one_order || units <= 0 || tiles < (rp.nslot >= 4 ? 6 : 12)) return 1;
+    if (rp.nslot <= 2 && rp.rowgroups == 1 && (units > kLightUnits || units > 5LL * tiles * rp.nslot)) return 1;
     const int per_cu = rp.nslot == 1 ? 4 : rp.nslot <= 3 ? 3 : 2;
     const int n = (int)std::min<long long>(std::min<long long>(256 * per_cu / units, tiles / kMinShareTiles), kMaxShares);
     if (n <= 1) return 1;
