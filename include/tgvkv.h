@@ -246,7 +246,8 @@ tgvkv_status tgvkv_compact(const tgvkv_problem* problem, const tgvkv_opts* opts,
  *
  * q      bf16 [B][L][heads_q][head_dim];  k_new, v_new bf16 [B][L][heads_kv][head_dim]
  * out    f32  [B][L][heads_q][head_dim]
- * workspace >= tgvkv_workspace_size(p, o, TGVKV_CALL_DECODE) (may be 0 bytes).
+ * workspace >= tgvkv_workspace_size(p, o, TGVKV_CALL_DECODE) (may be 0 bytes), with any first
+ *        contents; calls that may overlap need a workspace each.
  * unit_order_or_null  int32 [B*L], optional: the order in which (sequence, layer) units
  *        are dispatched, e.g. tgvkv_budget's longest-first order.  Results do not depend
  *        on it (each unit's arithmetic is the same); it only shortens the tail of a
@@ -271,8 +272,9 @@ tgvkv_status tgvkv_decode_attn(const tgvkv_problem* problem, const tgvkv_opts* o
  * looks the buffer's address up with that device current.
  * Limit: the partials must fit in 16 MiB, i.e. tgvkv_workspace_size(p, o,
  * TGVKV_CALL_DECODE) <= 16 MiB (every shape these kernels split stays below 9 MiB);
- * above it TGVKV_E_WORKSPACE and nothing is launched.  Every element of the buffer
- * that a call reads it first writes itself, so nothing is cleared between calls.
+ * above it TGVKV_E_WORKSPACE and nothing is launched.  The partials a call reads it
+ * writes itself, and it leaves its completion marks cleared, so nothing is cleared
+ * between calls.
  * Calls that overlap on one GPU (other streams or threads while one is in flight)
  * share that GPU's buffer and race: serialise them, or use tgvkv_decode_attn with a
  * workspace each.  Calls on different GPUs do not interact.
