@@ -686,15 +686,31 @@ hipError_t launch_score_text(const Shape& s, const RowPlan& rp, const uint16_t* 
     const int hsplit = s.G > 1 && nblk <= kHeadSplitUnits && !rp.one_order ? s.G : 1;
     const int G = s.G / hsplit;
     // the unit's text keys staged in LDS (text_pass_lds; in chunks of key blocks when they do not
-    // all fit beside the normalisers within 64 KB): against one wave per (unit, head, 16-key block)
-    // walking the row blocks from global memory, at llavanext 80 -> 20 us
+    // all fit beside the normalisers): against one wave per (unit, head, 16-key block) walking the row
+    // blocks from global memory, at llavanext 80 -> 20 us.  Within 40 KB, four workgroups per CU, when
+    // that leaves chunks of six key blocks, else within 64 KB: the pass is latency-bound, and 230 text
+    // rows took 85 us in one chunk with two workgroups per CU, 60 us in two chunks with four (224 units
+    // of 7 heads); 130 rows 47 and 43 us.
     const int TB = (s.Nt + 15) / 16;
     const long long head = ((long long)G * s.Nt * 4 + 15) / 16 * 16;
-    const long long kl = std::min<long long>(
-        (s.D == 128 ? text_part_bytes<128>(G, s.Nt) : text_part_bytes<64>(G, s.Nt)) + 16LL * TB * (2 * s.D + 16),
-        65536 - head);
     const int sys = lse_given ? 0 : s.Ns;
-    const bool staged = kl > 0 && !rp.one_order && (s.D == 128 ? text_lds_fits<128>(G, sys, s.Nt, kl) : text_lds_fits<64>(G, sys, s.Nt, kl));
+    long long kl = 0;  // 0: not staged
+    auto fit = [&](auto d) {
+        constexpr int D = decltype(d)::value;
+        for (const long long cap : {40960LL, 65536LL}) {
+            const long long k = std::min<long long>(text_part_bytes<D>(G, s.Nt) + 16LL * TB * Geo<D>::ROWB, cap - head);
+            if (k > 0 && text_lds_fits<D>(G, sys, s.Nt, k) &&
+                (cap == 65536LL || text_chunk_blocks<D>(G, s.Nt, k) >= std::min(TB, 6))) {
+                kl = k;
+                return;
+            }
+        }
+    };
+    if (!rp.one_order) {
+        if (s.D == 128) fit(IC<128>{});
+        else fit(IC<64>{});
+    }
+    const bool staged = kl > 0;
     if (lse_given && !staged) {
         const long long items = nblk * s.G * TB;
         if (s.D == 128)
@@ -710,10 +726,10 @@ hipError_t launch_score_text(const Shape& s, const RowPlan& rp, const uint16_t* 
     const int nsplit = ws_stat != nullptr ? stats_splits(s, rp) : 1;
     if (s.D == 128)
         hipLaunchKernelGGL(score_text_kernel<128>, grid, block, lds, st, s, q_text, k, lse, ws_vm, ws_colsum, ws_vmh,
-                           (int)lse_given, hsplit, staged ? kl : 0LL, ws_stat, nsplit, (int)rp.one_order);
+                           (int)lse_given, hsplit, kl, ws_stat, nsplit, (int)rp.one_order);
     else
         hipLaunchKernelGGL(score_text_kernel<64>, grid, block, lds, st, s, q_text, k, lse, ws_vm, ws_colsum, ws_vmh,
-                           (int)lse_given, hsplit, staged ? kl : 0LL, ws_stat, nsplit, (int)rp.one_order);
+                           (int)lse_given, hsplit, kl, ws_stat, nsplit, (int)rp.one_order);
     return hipGetLastError();
 }
 
