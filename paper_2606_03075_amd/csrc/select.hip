@@ -35,7 +35,7 @@ constexpr int kRegGroups = 12;  // most 64-position groups per wave kept in regi
 // Digits of the register select: two bins a thread.
 constexpr int digit_bits(int waves) { return waves >= 16 ? 11 : waves >= 8 ? 10 : 9; }
 enum { MODE_FORCED = 0, MODE_TEXT = 1, MODE_VIS = 2, MODE_JOINT = 3 };
-constexpr uint32_t kNotCand = 0u;  // keys of real candidates have the top bit or are >= 1
+constexpr uint32_t kNotCand = 0u;  // keys of candidates are >= 1 (RowCtx::key_of)
 
 struct RowCtx {
     int N, Ns, Nv, Nt, fs, fr;  // forced = [0, fs) U [fr, N)
@@ -51,12 +51,13 @@ struct RowCtx {
         if (mode == MODE_JOINT) return true;
         return mode == MODE_VIS ? is_vis(p) : !is_vis(p);
     }
-    // key of a candidate (only called when cand(p)) with score x; never kNotCand for finite scores.
+    // key of a candidate (only called when cand(p)) with score x; never kNotCand, whatever the score's bits
+    // (those of a NaN that are all ones would map to 0): the select counts on as many keys as candidates.
     // The forced positions all get one key, so the ties-to-lower-position rule takes the first ones.
     __device__ uint32_t key_of(int p, float x) const {
         if (mode == MODE_FORCED) return 1u;
         if (mode == MODE_JOINT && is_vis(p)) x *= vscale;
-        return ordered_key(x);
+        return max(ordered_key(x), 1u);
     }
     __device__ uint32_t key(int p) const {
         return key_of(p, is_vis(p) ? sv[p - Ns] : st[p < Ns ? p : p - Nv]);

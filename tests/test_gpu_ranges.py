@@ -170,6 +170,35 @@ def test_select_rows(lib, n, values):
             assert np.array_equal(got[offsets[l]:offsets[l + 1]], want), (l, joint)
 
 
+@pytest.mark.parametrize("n", [65, 769, 3073, 12288, 12289])
+def test_select_all_ones_scores(lib, n):
+    """Scores whose bits are all ones (a NaN, as in memory filled with 0xFF) are outside the contract, but they stay
+    candidates: below every number, the lower position first, every retained position written and in range."""
+    import torch
+    log(f"select all-ones scores {n}")
+    r = np.random.default_rng(n)
+    ns, nq, nv = 3, 5, n - 8
+    sv = r.standard_normal(nv).astype(np.float32)
+    number = r.random(nv) < 0.3
+    sv.view(np.uint32)[~number] = 0xFFFFFFFF
+    st = r.standard_normal(ns + nq).astype(np.float32)
+    few = int(number.sum())
+    bud = np.array([8 + few // 2, 8 + few, 9 + few, 8 + (few + nv) // 2, n - 1, n], np.int32)
+    offsets = O.flat_offsets(bud)
+    layers = len(bud)
+    idx = torch.full((int(offsets[-1]) + 64,), -1, dtype=torch.int32, device="cuda")
+    rows = [torch.from_numpy(np.broadcast_to(x, (1, layers, 1, x.size)).copy()).cuda() for x in (sv, st)]
+    bd.tgvkv_select(bd.make_problem(1, layers, 2, 2, 64, ns, nv, nq), None, *rows,
+                    torch.from_numpy(bud.reshape(1, layers)).cuda(), torch.from_numpy(offsets).cuda(), idx)
+    got = host(idx)
+    rank = np.lexsort((np.arange(nv), -np.where(number, sv, -np.inf)))  # numbers by value, then the others by position
+    text = np.concatenate([np.arange(ns), np.arange(ns + nv, n)])
+    for l, b in enumerate(bud):
+        want = np.sort(np.concatenate([text, ns + rank[:b - 8]]))
+        assert np.array_equal(got[offsets[l]:offsets[l + 1]], want), (l, int(b))
+    assert (got[offsets[-1]:] == -1).all()
+
+
 @pytest.mark.parametrize("heads_q,heads_kv,head_dim", [(2, 2, 128), (4, 2, 64), (8, 2, 128), (14, 2, 128), (16, 1, 64)])
 @pytest.mark.parametrize("segments", [1, 9, 16, 43, 64, 65, 128, 129])
 def test_split_decode(lib, segments, heads_q, heads_kv, head_dim):
