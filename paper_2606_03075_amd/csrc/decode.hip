@@ -13,8 +13,9 @@
 //     with every load unconditional, so the compiler's waits stay per block);
 //   * online softmax per lane group, merged across groups with wave shuffles and
 //     across the 4 waves through LDS; when the (sequence, layer, KV head) count is
-//     too small to fill the GPU the token range is split, and the unit's last workgroup to
-//     finish combines the partial (max, sum, weighted sum) triples (combine_splits).
+//     too small to fill the GPU, or a unit is long, the token range is split, and the unit's
+//     last workgroup to finish combines the partial (max, sum, weighted sum) triples
+//     (unit_splits, split_unit, combine_splits).
 // The step's new token is read from the k_new / v_new inputs (the cache slot it
 // is written to is not re-read in the same launch).  The cache is either one
 // contiguous segment per (sequence, layer) or fixed-size pages found through a
@@ -39,6 +40,8 @@ constexpr int kThreads = 256;
 // query heads per KV head from which decode runs on the matrix cores
 constexpr int kMfmaMinGroup = 3;
 constexpr int kMaxSplits = 8;  // of a unit's token range
+constexpr int kCUs = 256;
+constexpr int kMaxSplitGroups = 1024;  // workgroups of the units' splits, about
 
 __device__ __forceinline__ void unpack8(u32x4 r, float (&f)[8]) {
 #pragma unroll
@@ -59,10 +62,37 @@ __device__ __forceinline__ void unpack8(u32x4 r, float (&f)[8]) {
 // The marks live in the caller's workspace, whose first contents are unknown, so a mark is the number
 // of its call, 64 bits that differ between calls (counted from a scrambled clock).  A replayed graph
 // brings the same number again, but the last call on a workspace left its marks cleared.
-struct Arrivals {
-    unsigned long long* marks;  // [B*L*H_kv][splits], null without a split
+struct Splits {
+    unsigned long long* marks;  // [B*L*H_kv][most], null without a split
     unsigned long long call;    // never 0
+    int most, base;             // workgroups per unit; splits of a short unit
+    int rows;                   // rows per split of a longer one
+    int span;                   // units per 256 workgroups
 };
+
+// Splits of a unit of `len` rows (len is known on the device only).  The TVB budgets of one call differ by
+// an order of magnitude, and without more splits for its longest units these set the time: 160 units of
+// 400 to 4000 rows, mean 1500, one query head: 42.1 us with one workgroup each, 30.1 so; 132 units of up to
+// 10000 rows, seven query heads, 137 against 59.  Below kWholeRows a split costs more than it evens out
+// (160 units of 700 rows: 13.8 us whole, 16.6 in two).
+constexpr int kWholeRows = 1024;
+__device__ __forceinline__ int unit_splits(int len, const Splits& sp) {
+    const int n = len <= kWholeRows ? 1 : (len + sp.rows - 1) / sp.rows;
+    return min(max(sp.base, n), sp.most);
+}
+
+// The (unit, split) of a workgroup; false for none.  Each 256 workgroups, one per CU, hold every split of
+// the next `span` units, split by split.  Long units, which come first in the dispatch order, thus
+// spread over every CU; each 256 start `base` splits further on, so that short units' workgroups land
+// on CUs of their own, and every other 256 hold their units backwards, which evens the CUs' shares.
+// (A unit's splits next to one another left the active ones on a few XCDs when units are short: 112 units
+// of 1000 rows 30.4 us against 14.3.)
+__device__ __forceinline__ bool split_unit(const Splits& sp, int units, int bid, int& unit, int& split) {
+    const int row = bid / kCUs, blk = bid % kCUs / sp.span, j = bid % kCUs % sp.span;
+    unit = row * sp.span + ((row & 1) ? sp.span - 1 - j : j);
+    split = (blk + sp.most - row * sp.base % sp.most) % sp.most;
+    return blk < sp.most && unit < units;
+}
 
 // Partials pass between workgroups of different XCDs, whose L2 caches are apart.  They are written and
 // read as GPU-scope atomics, which go through to memory, so a finished store (vmcnt) is visible to the
@@ -78,20 +108,21 @@ __device__ __forceinline__ float load_shared(const float* p) {
 // Called by all threads of a workgroup after they wrote its partial of query heads bh0 .. bh0 + G - 1
 // (G <= GMAX).
 template <int D, int GMAX>
-__device__ __forceinline__ void combine_splits(const Arrivals& arr, size_t slot, int split, size_t bh0, int G, int nsplit,
+__device__ __forceinline__ void combine_splits(const Splits& sp, size_t slot, int split, size_t bh0, int G, int nsplit,
                                                const float* ws_part, float* __restrict__ out) {
     constexpr int ITERS = (GMAX * D + kThreads - 1) / kThreads;
     __shared__ int last;
     __shared__ float ml[2][GMAX][kMaxSplits];
     wait_vmem_all();  // this thread's part of the partial has reached memory (store_shared) ...
     __syncthreads();  // ... and every thread's has, before the arrival
-    unsigned long long* marks = arr.marks + slot * nsplit;
+    const int stride = sp.most;
+    unsigned long long* marks = sp.marks + slot * stride;
     if (threadIdx.x < 64) {
         if (threadIdx.x == 0)
-            __hip_atomic_store(marks + split, arr.call, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(marks + split, sp.call, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         wait_vmem_all();  // the mark has reached memory before the others' are read
         const bool here = threadIdx.x >= nsplit ||
-                          __hip_atomic_load(marks + threadIdx.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == arr.call;
+                          __hip_atomic_load(marks + threadIdx.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == sp.call;
         const bool all = __ballot(!here) == 0;
         if (threadIdx.x == 0) last = all;
     }
@@ -102,13 +133,13 @@ __device__ __forceinline__ void combine_splits(const Arrivals& arr, size_t slot,
 #pragma unroll
     for (int it = 0; it < ITERS; ++it) {
         const int x = min((int)threadIdx.x + it * kThreads, G * D - 1);
-        const float* p = ws_part + (bh0 + x / D) * nsplit * (size_t)(D + 2) + 2 + x % D;
+        const float* p = ws_part + (bh0 + x / D) * stride * (size_t)(D + 2) + 2 + x % D;
 #pragma unroll
         for (int i = 0; i < kMaxSplits; ++i) a[it][i] = load_shared(p + min(i, nsplit - 1) * (D + 2));
     }
     if (threadIdx.x < G * nsplit) {
         const int h = threadIdx.x / nsplit, i = threadIdx.x % nsplit;
-        const float* p = ws_part + ((bh0 + h) * nsplit + i) * (size_t)(D + 2);
+        const float* p = ws_part + ((bh0 + h) * stride + i) * (size_t)(D + 2);
         const float m = load_shared(p), l = load_shared(p + 1);
         ml[0][h][i] = m;
         ml[1][h][i] = l;
@@ -144,9 +175,8 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(Shape s, Rows rows, ui
                                                           const uint16_t* __restrict__ q,
                                                           const uint16_t* __restrict__ k_new,
                                                           const uint16_t* __restrict__ v_new, float* __restrict__ out,
-                                                          float* ws_part, int splits, Arrivals arr,
+                                                          float* ws_part, Splits sp,
                                                           const int32_t* __restrict__ unit_order) {
-    const int nsplit = SPLIT ? splits : 1;
     constexpr int LPR = D / 8;         // lanes per token row
     constexpr int GPW = 64 / LPR;      // lane groups per wave
     constexpr int NGRP = 4 * GPW;      // lane groups per workgroup
@@ -158,9 +188,9 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(Shape s, Rows rows, ui
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int sub = lane % LPR;
     const int grp = wave * GPW + lane / LPR;
-    int bid = blockIdx.x;
-    const int split = bid % nsplit;
-    bid /= nsplit;
+    int bid = blockIdx.x, split = 0;
+    if (SPLIT && !split_unit(sp, s.B * s.L * s.Hkv, blockIdx.x, bid, split)) return;
+    const int slot = bid;  // the unit's marks
     const int kvh = bid % s.Hkv;
     // dispatch order: unit_order[i] is the (sequence, layer) the i-th group of workgroups serves
     // (clamped, so a wrong order can never address outside the batch)
@@ -172,6 +202,8 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(Shape s, Rows rows, ui
     if (st < 0 || st >= reserve) return;  // uniform over the workgroup, before any barrier
     const int bsz = budgets[bl];
     const int len = bsz + st + 1;
+    const int nsplit = SPLIT ? unit_splits(len, sp) : 1;
+    if (SPLIT && split >= nsplit) return;  // uniform, before any barrier
     rows.init(s, bl, kvh, bsz, len, lds_pages);
     __syncthreads();
     const uint16_t* knew = k_new + ((size_t)bl * s.Hkv + kvh) * D;
@@ -323,10 +355,10 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(Shape s, Rows rows, ui
             }
         }
         const size_t bh = (size_t)bl * s.H + kvh * G + h;
-        if (!SPLIT) {
+        if (!SPLIT || nsplit == 1) {
             out[bh * D + dd] = num / den;
         } else {
-            float* p = ws_part + (bh * nsplit + split) * (size_t)(D + 2);
+            float* p = ws_part + (bh * sp.most + split) * (size_t)(D + 2);
             store_shared(p + 2 + dd, num);
             if (dd == 0) {
                 store_shared(p, M);
@@ -334,8 +366,10 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(Shape s, Rows rows, ui
             }
         }
     }
-    if constexpr (SPLIT)
-        combine_splits<D, GMAX>(arr, blockIdx.x / nsplit, split, (size_t)bl * s.H + kvh * G, G, nsplit, ws_part, out);
+    if constexpr (SPLIT) {
+        if (nsplit > 1)
+            combine_splits<D, GMAX>(sp, slot, split, (size_t)bl * s.H + kvh * G, G, nsplit, ws_part, out);
+    }
 }
 
 // Grouped-query decode on the matrix cores, for several query heads per KV head.
@@ -372,10 +406,8 @@ __global__ __launch_bounds__(kThreads) void decode_mfma_kernel(Shape s, Rows row
                                                                const uint16_t* __restrict__ q,
                                                                const uint16_t* __restrict__ k_new,
                                                                const uint16_t* __restrict__ v_new,
-                                                               float* __restrict__ out, float* ws_part, int splits,
-                                                               Arrivals arr,
+                                                               float* __restrict__ out, float* ws_part, Splits sp,
                                                                const int32_t* __restrict__ unit_order) {
-    const int nsplit = SPLIT ? splits : 1;
     constexpr int KSTEPS = D / 32;          // k-steps of S^T = K Q^T over the head dim
     constexpr int NB2 = D / 32;             // pairs of 16-dim output blocks
     constexpr int VROWB = D * 2 + 16;       // padded LDS row of the V stage, bytes
@@ -388,9 +420,9 @@ __global__ __launch_bounds__(kThreads) void decode_mfma_kernel(Shape s, Rows row
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int c = lane & 15, qq = lane >> 4;
-    int bid = blockIdx.x;
-    const int split = bid % nsplit;
-    bid /= nsplit;
+    int bid = blockIdx.x, split = 0;
+    if (SPLIT && !split_unit(sp, s.B * s.L * s.Hkv, blockIdx.x, bid, split)) return;
+    const int slot = bid;  // the unit's marks
     const int kvh = bid % s.Hkv;
     const int bl = unit_order != nullptr ? min(max(unit_order[bid / s.Hkv], 0), s.B * s.L - 1) : bid / s.Hkv;
     const int G = s.G;
@@ -399,6 +431,8 @@ __global__ __launch_bounds__(kThreads) void decode_mfma_kernel(Shape s, Rows row
     if (st < 0 || st >= reserve) return;  // uniform over the workgroup, before any barrier
     const int bsz = budgets[bl];
     const int len = bsz + st + 1;
+    const int nsplit = SPLIT ? unit_splits(len, sp) : 1;
+    if (SPLIT && split >= nsplit) return;  // uniform, before any barrier
     rows.init(s, bl, kvh, bsz, len, lds_pages);
     __syncthreads();
     const uint16_t* knew = k_new + ((size_t)bl * s.Hkv + kvh) * D;
@@ -564,10 +598,10 @@ __global__ __launch_bounds__(kThreads) void decode_mfma_kernel(Shape s, Rows row
             }
         }
         const size_t bh = (size_t)bl * s.H + kvh * G + h;
-        if (!SPLIT) {
+        if (!SPLIT || nsplit == 1) {
             out[bh * D + dd] = num / den;
         } else {
-            float* p = ws_part + (bh * nsplit + split) * (size_t)(D + 2);
+            float* p = ws_part + (bh * sp.most + split) * (size_t)(D + 2);
             store_shared(p + 2 + dd, num);
             if (dd == 0) {
                 store_shared(p, M);
@@ -575,23 +609,31 @@ __global__ __launch_bounds__(kThreads) void decode_mfma_kernel(Shape s, Rows row
             }
         }
     }
-    if constexpr (SPLIT)
-        combine_splits<D, GMAX>(arr, blockIdx.x / nsplit, split, (size_t)bl * s.H + kvh * G, G, nsplit, ws_part, out);
+    if constexpr (SPLIT) {
+        if (nsplit > 1)
+            combine_splits<D, GMAX>(sp, slot, split, (size_t)bl * s.H + kvh * G, G, nsplit, ws_part, out);
+    }
 }
 
 size_t partial_floats(const Shape& s, int nsplit) {
     return nsplit > 1 ? (size_t)s.B * s.L * s.H * nsplit * (s.D + 2) : 0;
 }
 
-// The call's marks (behind the partials, 8-byte aligned) and its number.
-Arrivals arrivals(const Shape& s, float* ws_part, int nsplit) {
-    if (nsplit <= 1) return Arrivals{nullptr, 0};
+// The call's splits: how units are split and dealt out, its marks (behind the partials, 8-byte aligned)
+// and its number.
+Splits call_splits(const Shape& s, float* ws_part, int nsplit) {
+    if (nsplit <= 1) return Splits{nullptr, 0, 1, 1, 1, 1};
     static std::atomic<unsigned long long> next{
         (unsigned long long)std::chrono::steady_clock::now().time_since_epoch().count() * 0x9E3779B97F4A7C15ull};
+    const int units = s.B * s.L * s.Hkv;  // at most 512, for a split
     unsigned long long call;
     do call = next.fetch_add(1, std::memory_order_relaxed); while (call == 0);
     const uintptr_t end = reinterpret_cast<uintptr_t>(ws_part + partial_floats(s, nsplit));
-    return Arrivals{reinterpret_cast<unsigned long long*>((end + 7) / 8 * 8), call};
+    return Splits{reinterpret_cast<unsigned long long*>((end + 7) / 8 * 8), call, nsplit,
+                  std::min(std::max(kCUs / units, 1), nsplit),
+                  // more units than CUs are even enough without the shorter splits (400 units of 1000 rows: 35 us
+                  // against 44 in two splits)
+                  units <= kCUs ? 512 : 1024, kCUs / nsplit};
 }
 
 template <int D, class Rows>
@@ -599,11 +641,12 @@ hipError_t launch_decode_d(const Shape& s, const Rows& rows, size_t lds_bytes, u
                            const int32_t* budgets, int32_t reserve, int32_t step, const int32_t* steps,
                            const uint16_t* q, const uint16_t* k_new, const uint16_t* v_new, float* out, float* ws_part,
                            int nsplit, const int32_t* unit_order, hipStream_t st) {
-    dim3 grid((unsigned)((long long)s.B * s.L * s.Hkv * nsplit)), block(kThreads);
-    const Arrivals arr = arrivals(s, ws_part, nsplit);
+    const Splits sp = call_splits(s, ws_part, nsplit);
+    const long long units = (long long)s.B * s.L * s.Hkv;
+    const dim3 grid((unsigned)(nsplit > 1 ? (units + sp.span - 1) / sp.span * kCUs : units)), block(kThreads);
     auto launch = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, grid, block, lds_bytes, st, s, rows, kc, vc, budgets, reserve, step, steps, q, k_new,
-                           v_new, out, ws_part, nsplit, arr, unit_order);
+                           v_new, out, ws_part, sp, unit_order);
     };
     if (nsplit > 1) {
         if (s.G <= 1) launch(decode_kernel<D, 1, Rows, true>);
@@ -628,6 +671,9 @@ hipError_t launch_decode_d(const Shape& s, const Rows& rows, size_t lds_bytes, u
 // name to a kernel (it is a host-side stand-in there); decode_scratch() gives its device
 // address, looked up once per device with that device current.
 static __device__ __align__(256) float scratch[kDecodeScratchBytes / sizeof(float)];
+// every shape that is split fits: 16 query heads at most (decode_mfma_kernel), head_dim 128
+static_assert(kMaxSplitGroups * (16 * (128 + 2) * sizeof(float) + sizeof(unsigned long long)) + 256 <= kDecodeScratchBytes,
+              "split partials and marks in the static buffer");
 
 hipError_t decode_scratch(float** ptr) {
     constexpr int kMaxDevices = 64;
@@ -651,13 +697,13 @@ hipError_t decode_scratch(float** ptr) {
 int decode_splits(const Shape& s) {
     const long long units = (long long)s.B * s.L * s.Hkv;
     if (units <= 0) return 1;
-    // split a unit's tokens only while the workgroups fit one per CU: a partial costs its trip
-    // through memory and the combination about 4 us at the end, and one workgroup's waves already keep
-    // a CU's share of the stream in flight.  Against splitting up to 1024 workgroups (4 per CU), per
-    // step: 128 units of 300 rows 9.9 against 12.1 us, 256 units of 300 rows 10.2 against 13.5, 112
-    // units of 830 rows 15.9 against 19.2 and of 4200 rows 43.5 against 50.0, 512 units of 440 rows
-    // 22.2 against 26.3; at 32 units (8 splits either way) 11.7.
-    long long n = 256 / units;
+    // most workgroups per unit: about 1024 in all, 4 per CU; a unit takes as many of them as its rows are
+    // worth (unit_splits), at least as many as fit one per CU: a partial costs its trip through memory and
+    // the combination about 4 us at the end, and one workgroup's waves already keep a CU's share of the
+    // stream in flight.  Against as many splits as workgroups for every unit, of even lengths, per step: 132
+    // units of 300 rows 9.0 against 12.8 us, 112 units of 1000 rows 14.2 against 16.0; 32 units (8
+    // splits either way) 7.7.
+    long long n = kMaxSplitGroups / units;
     if (n < 1) n = 1;
     if (n > kMaxSplits) n = kMaxSplits;
     return (int)n;

@@ -71,6 +71,16 @@ def test_workspace_size(lib):
     assert bd.workspace_size(P(batch=64, layers=32, heads_q=32, heads_kv=32), None, bd.CALL_DECODE) == 0
 
 
+@pytest.mark.parametrize("units,splits", [(1, 8), (128, 8), (129, 7), (160, 6), (256, 4), (257, 3), (512, 2), (513, 1)])
+def test_long_decode_units_can_be_split(lib, units, splits):
+    """Decode calls of up to 512 units have workgroups to share out their longest units (from 129 to 512 units one
+    workgroup each had taken up to 2.3 times as long): the workspace holds each split's partials and mark."""
+    need = bd.workspace_size(P(batch=units, layers=1, heads_q=7, heads_kv=1, n_vis=8192), None, bd.CALL_DECODE)
+    least = units * splits * (7 * (128 + 2) * 4 + 8) if splits > 1 else 0
+    assert least <= need <= least + 512 and (need > 0) == (splits > 1)
+    assert need <= 9 << 20
+
+
 @pytest.mark.skipif(_gpu(), reason="fake pointers are used only where no GPU exists")
 def test_validation_before_any_launch(lib):
     fake = ctypes.c_void_p(0x10000)

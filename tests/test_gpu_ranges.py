@@ -199,42 +199,62 @@ def test_select_all_ones_scores(lib, n):
     assert (got[offsets[-1]:] == -1).all()
 
 
-@pytest.mark.parametrize("heads_q,heads_kv,head_dim", [(2, 2, 128), (4, 2, 64), (8, 2, 128), (14, 2, 128), (16, 1, 64)])
-@pytest.mark.parametrize("segments", [1, 9, 16, 43, 64, 65, 128, 129])
-def test_split_decode(lib, segments, heads_q, heads_kv, head_dim):
-    """Decode around the unit counts where a unit's tokens are split (up to 256 units), its partials combined by the
-    unit's last workgroup: any first contents of the workspace, and call after call on the same workspace.
+def decode_steps(bud, heads_q, heads_kv, head_dim, reserve, steps, fill, order=None):
+    """Decode steps on one workspace with given first contents, each against 64 bits.
 
     Outputs are means of values near 1 under probabilities of 16 bits or more: within 1e-4 of 64 bits."""
     import torch
-    log(f"split decode {segments} segments {heads_q}/{heads_kv} d{head_dim}")
+    segments = len(bud)
     g = torch.Generator(device="cuda")
     g.manual_seed(segments)
-    r = np.random.default_rng(segments)
-    reserve, steps = 3, 3
-    bud = r.integers(0, 200, segments).astype(np.int32)
-    bud[0] = 0
-    p = bd.make_problem(1, segments, heads_q, heads_kv, head_dim, 4, 300, 8)
+    p = bd.make_problem(1, segments, heads_q, heads_kv, head_dim, 4, max(300, int(bud.max())), 8)
     seg = np.concatenate([[0], np.cumsum(bud.astype(np.int64) + reserve)])
     cache = [torch.randn(int(seg[-1]) * heads_kv * head_dim, generator=g, device="cuda", dtype=torch.bfloat16)
              for _ in range(2)]
     need = bd.workspace_size(p, None, bd.CALL_DECODE)
-    assert (need > 0) == (segments * heads_kv <= 128)
+    assert (need > 0) == (segments * heads_kv <= 512)
     out = torch.empty(1, segments, heads_q, head_dim, device="cuda")
+    ws = torch.randint(0, 256, (max(need, 1),), generator=g, device="cuda", dtype=torch.uint8)
+    if fill == "ones":
+        ws.fill_(255)
+    for step in range(steps):
+        q, kn, vn = (torch.randn(1, segments, h, head_dim, generator=g, device="cuda", dtype=torch.bfloat16)
+                     for h in (heads_q, heads_kv, heads_kv))
+        out.fill_(float("nan"))
+        bd.tgvkv_decode_attn(p, None, *cache, torch.from_numpy(bud).cuda(), torch.from_numpy(seg).cuda(), reserve,
+                             step, q, kn, vn, out, ws,
+                             unit_order=None if order is None else torch.from_numpy(order).cuda())
+        for l in range(segments):
+            n, cap = int(bud[l]) + step + 1, int(bud[l]) + reserve
+            k, v = (c[seg[l] * heads_kv * head_dim:seg[l + 1] * heads_kv * head_dim].view(heads_kv, cap, head_dim)
+                    [:, :n].double() for c in cache)
+            assert torch.equal(k[:, -1], kn[0, l].double())
+            z = torch.matmul(q[0, l].double().view(heads_kv, -1, head_dim), k.transpose(1, 2).contiguous())
+            want = torch.matmul(torch.softmax(z / head_dim ** 0.5, -1), v).view(heads_q, head_dim)
+            assert (out[0, l].double() - want).abs().max().item() <= 1e-4, (fill, step, l)
+
+
+@pytest.mark.parametrize("heads_q,heads_kv,head_dim", [(2, 2, 128), (4, 2, 64), (8, 2, 128), (14, 2, 128), (16, 1, 64)])
+@pytest.mark.parametrize("segments", [1, 9, 16, 43, 64, 65, 128, 129, 170, 171, 256, 257])
+def test_split_decode(lib, segments, heads_q, heads_kv, head_dim):
+    """Decode around the unit counts where the workgroups per unit change (up to 512 units have more than one), the
+    partials combined by the unit's last workgroup: any first contents of the workspace, and call after call on it."""
+    log(f"split decode {segments} segments {heads_q}/{heads_kv} d{head_dim}")
+    bud = np.random.default_rng(segments).integers(0, 200, segments).astype(np.int32)
+    bud[0] = 0
     for fill in ("random", "ones"):
-        ws = torch.randint(0, 256, (max(need, 1),), generator=g, device="cuda", dtype=torch.uint8)
-        if fill == "ones":
-            ws.fill_(255)
-        for step in range(steps):
-            q, kn, vn = (torch.randn(1, segments, h, head_dim, generator=g, device="cuda", dtype=torch.bfloat16)
-                         for h in (heads_q, heads_kv, heads_kv))
-            bd.tgvkv_decode_attn(p, None, *cache, torch.from_numpy(bud).cuda(), torch.from_numpy(seg).cuda(), reserve,
-                                 step, q, kn, vn, out, ws)
-            for l in range(segments):
-                n, cap = int(bud[l]) + step + 1, int(bud[l]) + reserve
-                k, v = (c[seg[l] * heads_kv * head_dim:seg[l + 1] * heads_kv * head_dim].view(heads_kv, cap, head_dim)
-                        [:, :n].double() for c in cache)
-                assert torch.equal(k[:, -1], kn[0, l].double())
-                z = torch.matmul(q[0, l].double().view(heads_kv, -1, head_dim), k.transpose(1, 2).contiguous())
-                want = torch.matmul(torch.softmax(z / head_dim ** 0.5, -1), v).view(heads_q, head_dim)
-                assert (out[0, l].double() - want).abs().max().item() <= 1e-4, (fill, step, l)
+        decode_steps(bud, heads_q, heads_kv, head_dim, 3, 3, fill)
+
+
+@pytest.mark.parametrize("heads_q,heads_kv,head_dim", [(4, 4, 128), (4, 2, 64), (28, 4, 128), (32, 4, 64)])
+@pytest.mark.parametrize("segments", [5, 33, 56, 75, 128])
+def test_split_decode_of_uneven_lengths(lib, segments, heads_q, heads_kv, head_dim):
+    """Units of one row to several thousand in one call, longest first as a budget call orders them and in no order:
+    each takes its own number of splits, the lengths where it changes among them."""
+    log(f"uneven split decode {segments} segments {heads_q}/{heads_kv} d{head_dim}")
+    r = np.random.default_rng(segments)
+    bud = np.exp(r.uniform(0, np.log(5000), segments)).astype(np.int32)
+    edges = [0, 1021, 1023, 1024, 2047, 2048, 5000]  # rows of a call: budget + step + 1
+    bud[r.permutation(segments)[:len(edges)]] = edges[:segments]
+    for order in (np.argsort(-bud, kind="stable").astype(np.int32), None):
+        decode_steps(bud, heads_q, heads_kv, head_dim, 2, 2, "random", order)
