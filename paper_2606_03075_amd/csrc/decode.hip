@@ -97,7 +97,9 @@ __device__ __forceinline__ bool split_unit(const Splits& sp, int units, int bid,
 // Partials pass between workgroups of different XCDs, whose L2 caches are apart.  They are written and
 // read as GPU-scope atomics, which go through to memory, so a finished store (vmcnt) is visible to the
 // whole GPU and no cache has to be written back or dropped: with plain stores and a GPU-scope fence
-// on either side, whose write-back covers the whole L2, the step took 48 us.
+// on either side, whose write-back covers the whole L2, the step took 48 us.  That relies on gfx950, where
+// such accesses write and read through; in the language relaxed atomics order nothing between them, so
+// the waits in between hold the compiler too (wait_vmem_ordered).
 __device__ __forceinline__ void store_shared(float* p, float v) {
     __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -113,14 +115,14 @@ __device__ __forceinline__ void combine_splits(const Splits& sp, size_t slot, in
     constexpr int ITERS = (GMAX * D + kThreads - 1) / kThreads;
     __shared__ int last;
     __shared__ float ml[2][GMAX][kMaxSplits];
-    wait_vmem_all();  // this thread's part of the partial has reached memory (store_shared) ...
+    wait_vmem_ordered();  // this thread's part of the partial has reached memory (store_shared) ...
     __syncthreads();  // ... and every thread's has, before the arrival
     const int stride = sp.most;
     unsigned long long* marks = sp.marks + slot * stride;
     if (threadIdx.x < 64) {
         if (threadIdx.x == 0)
             __hip_atomic_store(marks + split, sp.call, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        wait_vmem_all();  // the mark has reached memory before the others' are read
+        wait_vmem_ordered();  // the mark has reached memory before the others' are read
         const bool here = threadIdx.x >= nsplit ||
                           __hip_atomic_load(marks + threadIdx.x, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == sp.call;
         const bool all = __ballot(!here) == 0;

@@ -54,6 +54,10 @@ __device__ __forceinline__ void settle(const T& v) {
 // waits for every vector memory access of the wave, stores included.
 __device__ __forceinline__ void wait_vmem_all() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 
+// The same wait, across which the compiler moves no memory access either (to the compiler the builtin above is
+// no memory operation): for a store that has to have reached memory before the next access is made.
+__device__ __forceinline__ void wait_vmem_ordered() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // v_exp_f32: 2^x, exp2(-inf) = 0.
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
