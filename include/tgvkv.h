@@ -100,11 +100,10 @@ enum {
     TGVKV_SCORE_TEXT   = 2,  /* text scores s^T, weights w~, per-layer text->vision mass      */
     TGVKV_SCORE_VISION = 4,  /* text-weighted vision scores s^V                               */
     TGVKV_SCORE_ALL    = 7,
-    TGVKV_SCORE_ONE_ORDER = 32,/* with any phases, not with LSE_IN: every sum in an order that depends on the sequence's
-                                own shape only, so a sequence gets the same scores, bit for bit, in
-                                any batch (and the same positions are retained from them).  Without
-                                it a batch of few (sequence, layer, KV head) units is spread over
-                                more workgroups: faster, the last bits differ.                   */
+    TGVKV_SCORE_ONE_ORDER = 32,/* with any phases, not with LSE_IN: each unit's keys are summed in one run, not
+                                in the shares that let a sequence of few (layer, KV head) units use
+                                more of the GPU.  The last bits differ; positions retained from
+                                these scores can differ where two scores almost tie.             */
     TGVKV_SCORE_LSE_IN = 16  /* with exactly TEXT|VISION: lse is an input holding every text
                                 row's normaliser, as a prefill attention kernel returns it;
                                 the statistics sweep is skipped, the vision sweep also gives
@@ -142,6 +141,8 @@ enum { TGVKV_CALL_SCORE = 0, TGVKV_CALL_DECODE = 1 };
  *                  left untouched.
  * phases  any non-empty OR of STATS, TEXT, VISION; or exactly TEXT|VISION|LSE_IN
  *         (see TGVKV_SCORE_LSE_IN).  ONE_ORDER is given with all phases of a pass or with none.
+ *         With it or without it the order of every sum depends on the sequence's own shape only:
+ *         a sequence gets the same scores, bit for bit, in any batch (not so tv_mass with LSE_IN).
  *         Phases must run in the order STATS, TEXT, VISION, with the same
  *         workspace and outputs; a later phase reads what the earlier ones left
  *         there.  Pointers of phases not requested may be NULL (lse is needed by

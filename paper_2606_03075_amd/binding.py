@@ -21,7 +21,7 @@ LIB_PATH = os.environ.get("TGVKV_LIBRARY") or os.path.join(_HERE, "libtgvkv.so")
 TGVKV_OK, TGVKV_E_INVAL, TGVKV_E_UNSUPPORTED, TGVKV_E_WORKSPACE, TGVKV_E_CAPACITY, TGVKV_E_HIP = 0, -1, -2, -3, -4, -5
 SCORE_STATS, SCORE_TEXT, SCORE_VISION, SCORE_ALL = 1, 2, 4, 7
 SCORE_LSE_IN = 16  # lse holds the text rows' normalisers from the caller's prefill: K is read once
-SCORE_ONE_ORDER = 32  # with any phases: a sequence's scores are the same, bit for bit, in any batch
+SCORE_ONE_ORDER = 32  # with any phases: every unit's keys summed in one run, not in shares
 CALL_SCORE, CALL_DECODE = 0, 1
 
 ABI_VERSION = 8  # TGVKV_ABI_VERSION of the library this binding marshals for
@@ -439,9 +439,10 @@ class EvictionBuffers:
         launch, vision scores for every layer) or 'lse_in' (self.lse
         already holds every text row's normaliser from the caller's prefill: text and vision
         scores and the TV mass in one K pass, then the budgets).  marks(name) is called after
-        each stage (for event timing).  Except in 'lse_in', the scores are taken in the order of
-        sums that does not depend on the batch, so a sequence keeps the same positions whatever
-        shares its batch.
+        each stage (for event timing).  The order of sums depends on the sequence's own shape only,
+        so a sequence keeps the same positions whatever shares its batch (in 'lse_in' the
+        layers' masses, and with them the budgets, may differ in the last bits).  Except in
+        'lse_in' it is SCORE_ONE_ORDER's.
         """
         mark = marks if marks is not None else (lambda name: None)
         sched = self.schedule() if schedule == "auto" else schedule

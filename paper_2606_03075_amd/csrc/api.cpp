@@ -134,10 +134,10 @@ ScoreWs score_workspace(const Shape& s, const RowPlan& rp, void* base) {
     off = align_up(off + sizeof(float) * bl * s.H);
     w.part = reinterpret_cast<float*>(b ? b + off : nullptr);
     off = align_up(off + sizeof(float) * bl * s.Hkv * (size_t)std::max(rp.rowgroups, 1) * s.Nv);
-    // a split statistics sweep: [3][splits][B*L*H][N_q] partial row statistics
-    const int ss = tgvkv::stats_splits(s, rp);
+    // shares of their own workgroups: [3][key parts][splits][B*L*H][N_q] partial row statistics
+    const int ss = tgvkv::stats_spread(s, rp) ? tgvkv::stats_splits(s, rp) : 1;
     w.stat = reinterpret_cast<float*>(b && ss > 1 ? b + off : nullptr);
-    if (ss > 1) off = align_up(off + sizeof(float) * 3 * (size_t)ss * bl * s.H * s.Nq);
+    if (ss > 1) off = align_up(off + sizeof(float) * 3 * (size_t)rp.ks * ss * bl * s.H * s.Nq);
     w.bytes = off;
     return w;
 }

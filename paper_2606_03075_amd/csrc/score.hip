@@ -13,8 +13,8 @@
 //                 workgroup, when one workgroup holds all of a unit's question rows;
 //   score_text    text rows x text keys: system-row normalisers, then the
 //                 text->text probabilities' column sums per head (Eq. (9)); with few units
-//                 sweep 1 is split over the keys, and this merges the shares' statistics
-//                 (score_stats_merge does when the statistics are asked for alone);
+//                 sweep 1's shares of the keys have workgroups of their own, and this merges
+//                 their statistics (score_stats_merge does when these are asked for alone);
 //   score_fin     head means -> s^T, w, w~ (Eq. (7), (9)) and the layer's
 //                 text->vision mass (Eq. (5)-(6));
 //   score_vision  sweep 2: question rows x vision keys, p = exp(z - lse),
@@ -39,31 +39,75 @@ namespace {
 
 using namespace core;
 
-// Partial row statistics of a sweep whose keys are split over nsplit workgroups: [3][nsplit][rows]
-// (reference max in base-2 units, sum, vision sum), rows = B*L*H*N_q.  merge_row adds a row's
-// shares in share order and gives its normaliser (natural log) and vision mass.
-__device__ __forceinline__ void merge_row(const float* __restrict__ ws_stat, size_t rows, int nsplit, size_t r,
+// Partial row statistics of a sweep whose keys are summed in nsplit shares, of ks key parts each:
+// [3][ks][nsplit][rows] (reference max in base-2 units, sum, vision sum), rows = B*L*H*N_q.  merge_row adds
+// a row's shares in share order, then its key parts, and gives its normaliser (natural log) and vision mass.
+__device__ __forceinline__ void merge_row(const float* ws_stat, size_t rows, int nsplit, int ks, size_t r,
                                           float& ln, float& vm) {
-    const size_t plane = rows * nsplit;
-    float m = ws_stat[r], l = ws_stat[plane + r], v = ws_stat[2 * plane + r];
-#pragma unroll 4
-    for (int sp = 1; sp < nsplit; ++sp) {
-        const size_t x = sp * rows + r;
-        merge_stats(m, l, v, ws_stat[x], ws_stat[plane + x], ws_stat[2 * plane + x]);
+    const size_t plane = rows * nsplit * ks;
+    float m = kNegInf, l = 0.f, v = 0.f;
+    for (int kp = 0; kp < ks; ++kp) {
+        const float* w = ws_stat + (size_t)kp * nsplit * rows + r;
+        float pm = w[0], pl = w[plane], pv = w[2 * plane];
+        constexpr int U = 6;  // shares' loads in flight at once
+        for (int s0 = 1; s0 < nsplit; s0 += U) {
+            float a[U][3];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const size_t x = min(s0 + u, nsplit - 1) * rows;
+                a[u][0] = w[x];
+                a[u][1] = w[plane + x];
+                a[u][2] = w[2 * plane + x];
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u)
+                if (s0 + u < nsplit) merge_shares(pm, pl, pv, a[u][0], a[u][1], a[u][2]);
+        }
+        if (kp == 0) {
+            m = pm;
+            l = pl;
+            v = pv;
+        } else {
+            merge_shares(m, l, v, pm, pl, pv);
+        }
     }
     ln = (m + log2f(l)) * kLn2;
     vm = v / l;
 }
 
-// Sweep 1 of one share of a unit's keys, for one row group.  With few units one workgroup per
-// unit leaves most of the chip idle, so the keys are split over nsplit workgroups (stats_splits);
-// the shares' statistics are merged by the text pass or by score_stats_merge.
-template <int D, int NSLOT, int KS>
+// Keys of share sp of a unit, a multiple of the tile, and its partial statistics for the row group that
+// starts at block rb0.
+template <int NSLOT, int KS>
+__device__ __forceinline__ void write_share(const Shape& s, int bl, int kvh, int rb0, int sp, int nsplit,
+                                            const int (&qrow)[NSLOT], const float (&m)[NSLOT],
+                                            const float (&lsum)[NSLOT], const float (&vsum)[NSLOT], float* ws_stat) {
+    constexpr int RSETS = 4 / KS;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int rs = wave % RSETS, kp = wave / RSETS;
+    const int QB = (s.Nq + 15) >> 4, NB = s.G * QB;
+    if (lane >= 16) return;
+    const size_t rows = (size_t)s.B * s.L * s.H * s.Nq;
+#pragma unroll
+    for (int sl = 0; sl < NSLOT; ++sl) {
+        const int rb = slot_block<RSETS>(rb0, rs, sl);
+        const int qi = qrow[sl];
+        if (rb < NB && qi < s.Nq) {
+            float* w = ws_stat + (kp * nsplit + sp) * rows + ((size_t)bl * s.H + kvh * s.G + rb / QB) * s.Nq + qi;
+            w[0] = m[sl];
+            w[rows * nsplit * KS] = lsum[sl];
+            w[2 * rows * nsplit * KS] = vsum[sl];
+        }
+    }
+}
+
+// Sweep 1 of one row group of a unit: of one of its nsplit shares of `per` key tiles, whose statistics the
+// text pass or score_stats_merge merges, or (nsplit 1) of all its keys, with SHARES in shares of `per` tiles.
+template <int D, int NSLOT, int KS, bool SHARES>
 __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(NSLOT >= 6 ? 2 : NSLOT == 3 ? 3 : 1))) void score_stats_kernel(Shape s, int rowgroups,
                                                                const uint16_t* __restrict__ q_text,
                                                                const uint16_t* __restrict__ k,
                                                                float* __restrict__ lse,
-                                                               float* __restrict__ ws_vm, int nsplit,
+                                                               float* __restrict__ ws_vm, int nsplit, int per,
                                                                float* __restrict__ ws_stat) {
     constexpr int RSETS = 4 / KS;
     __shared__ __attribute__((aligned(16))) char tiles[2][Geo<D>::TILE_BYTES];
@@ -83,28 +127,24 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(NSLOT 
     bf16x8 qf[NSLOT][Geo<D>::KSTEPS];
     int qrow[NSLOT];
     load_qrows<D, NSLOT, KS>(s, q_text, bl, kvh, rb0, qf, qrow);
-    float m[NSLOT], lsum[NSLOT], vsum[NSLOT];
     const uint16_t* kbase = k + ((size_t)bl * s.Hkv + kvh) * (size_t)s.N * D;
-    const int per = ((s.N + kTile - 1) / kTile + nsplit - 1) / nsplit * kTile;  // keys per share
-    const int kbeg = min(sp * per, s.N), kend = min(kbeg + per, s.N);
-    stats_sweep<D, NSLOT, KS>(s, kbase, kbeg, kend, qf, qrow, tiles, m, lsum, vsum);
-    if (kp == 0 && lane < 16) {
-        const size_t rows = (size_t)s.B * s.L * s.H * s.Nq;
+    const int kbeg = sp * per * kTile, kend = min(kbeg + per * kTile, s.N);
+    float m[NSLOT], lsum[NSLOT], vsum[NSLOT];
+    if constexpr (SHARES)
+        stats_sweep<D, NSLOT, KS, true>(s, kbase, 0, s.N, qf, qrow, tiles, m, lsum, vsum, per);
+    else
+        stats_sweep<D, NSLOT, KS>(s, kbase, kbeg, kend, qf, qrow, tiles, m, lsum, vsum, 0, nsplit > 1);
+    if (!SHARES && nsplit > 1) {
+        write_share<NSLOT, KS>(s, bl, kvh, rb0, sp, nsplit, qrow, m, lsum, vsum, ws_stat);
+    } else if (kp == 0 && lane < 16) {
 #pragma unroll
         for (int sl = 0; sl < NSLOT; ++sl) {
             const int rb = slot_block<RSETS>(rb0, rs, sl);
             const int qi = qrow[sl];
             if (rb < NB && qi < s.Nq) {
                 const size_t head = (size_t)bl * s.H + kvh * s.G + rb / QB;
-                if (nsplit > 1) {
-                    float* w = ws_stat + sp * rows + head * s.Nq + qi;
-                    w[0] = m[sl];
-                    w[rows * nsplit] = lsum[sl];
-                    w[2 * rows * nsplit] = vsum[sl];
-                } else {
-                    lse[head * s.Nt + s.Ns + qi] = (m[sl] + log2f(lsum[sl])) * kLn2;
-                    ws_vm[head * s.Nq + qi] = vsum[sl] / lsum[sl];
-                }
+                lse[head * s.Nt + s.Ns + qi] = (m[sl] + log2f(lsum[sl])) * kLn2;
+                ws_vm[head * s.Nq + qi] = vsum[sl] / lsum[sl];
             }
         }
     }
@@ -113,13 +153,13 @@ __global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(NSLOT 
 // Normalisers and vision masses from the shares' statistics, one thread per question row (for
 // calls that ask for the statistics alone; the text pass merges them itself).
 __global__ __launch_bounds__(kThreads) void score_stats_merge_kernel(Shape s, const float* __restrict__ ws_stat,
-                                                                     int nsplit, float* __restrict__ lse,
+                                                                     int nsplit, int ks, float* __restrict__ lse,
                                                                      float* __restrict__ ws_vm) {
     const size_t rows = (size_t)s.B * s.L * s.H * s.Nq;
     const size_t r = (size_t)blockIdx.x * kThreads + threadIdx.x;
     if (r >= rows) return;
     float ln, vm;
-    merge_row(ws_stat, rows, nsplit, r, ln, vm);
+    merge_row(ws_stat, rows, nsplit, ks, r, ln, vm);
     lse[r / s.Nq * s.Nt + s.Ns + r % s.Nq] = ln;
     ws_vm[r] = vm;
 }
@@ -143,11 +183,13 @@ constexpr bool kQregsText = (NSLOT == 3 || NSLOT == 4) && KS == 1;
 // pass), and at the 13B stress shape it took 6.84 ms against 7.21-7.25 ms at 2 waves per SIMD.
 // QREGS: a kernel of its own for text mode 2, without the other modes' code: their calls beside the
 // spills at 168 registers cost the 13B stress shape 5 %.
-template <int D, int NSLOT, int KS, bool QREGS = false>
-__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(NSLOT == 3 || NSLOT == 4 ? 3 : 1))) void
+// SHARES: the unit's keys are summed in shares of share_tiles tiles and the text pass's columns BY_ROW, to the
+// bits of score_stats on every share and score_text.
+template <int D, int NSLOT, int KS, bool QREGS = false, bool SHARES = false>
+__global__ __launch_bounds__(kThreads) __attribute__((amdgpu_waves_per_eu(NSLOT == 3 || NSLOT == 4 ? 3 : SHARES && NSLOT == 6 && D == 128 ? 2 : 1))) void
 score_stats_text_kernel(Shape s, const uint16_t* __restrict__ q_text, const uint16_t* __restrict__ k,
                         float* __restrict__ lse, float* __restrict__ ws_vm, float* __restrict__ ws_colsum,
-                        float* __restrict__ ws_vmh, int text_mode) {
+                        float* __restrict__ ws_vmh, int text_mode, int share_tiles) {
     constexpr int RSETS = 4 / KS;
     __shared__ __attribute__((aligned(16))) char tiles[2][Geo<D>::TILE_BYTES];
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -163,7 +205,7 @@ score_stats_text_kernel(Shape s, const uint16_t* __restrict__ q_text, const uint
     load_qrows<D, NSLOT, KS>(s, q_text, bl, kvh, 0, qf, qrow);
     float m[NSLOT], lsum[NSLOT], vsum[NSLOT];
     const uint16_t* kbase = k + ((size_t)bl * s.Hkv + kvh) * (size_t)s.N * D;
-    stats_sweep<D, NSLOT, KS>(s, kbase, 0, s.N, qf, qrow, tiles, m, lsum, vsum);
+    stats_sweep<D, NSLOT, KS, SHARES>(s, kbase, 0, s.N, qf, qrow, tiles, m, lsum, vsum, share_tiles);
 
     // [G][N_t] normalisers (base 2), then [G][N_q] vision masses: in the dynamic LDS area
     // (text mode 2, whose text pass streams keys through the tiles), else in the freed tiles
@@ -200,35 +242,27 @@ score_stats_text_kernel(Shape s, const uint16_t* __restrict__ q_text, const uint
         // the question rows' fragments are still in registers: only text keys are loaded
         text_pass_qregs<D, NSLOT, KS>(s, bl, kvh, q_text, k, lse, qf, lse2s, vms + (size_t)s.G * s.Nq, tiles,
                                       ws_colsum);
-    } else if (text_mode == 1) {
+    } else if (SHARES || text_mode == 1) {
         // the unit's text keys go into the freed tiles after the normalisers and masses
         const size_t off = ((size_t)s.G * (s.Nt + s.Nq) * sizeof(float) + 15) & ~(size_t)15;
-        text_pass_lds<D>(s, bl, kvh, 0, s.G, q_text, k, lse, lse2s, &tiles[0][0] + off,
+        text_pass_lds<D, SHARES>(s, bl, kvh, 0, s.G, q_text, k, lse, lse2s, &tiles[0][0] + off,
                          2LL * Geo<D>::TILE_BYTES - (long long)off, ws_colsum);
     } else {
         text_pass<D>(s, bl, kvh, 0, s.G, q_text, k, lse, lse2s, ws_colsum);
     }
 }
 
-// The text pass of one unit, or with hsplit > 1 of one of its query heads (hsplit = G).
-// ws_stat non-null: the question rows' statistics come as nsplit shares, merged here.
+// The text pass of query heads g0 .. g0 + G - 1 of one unit by one workgroup.  ws_stat non-null: the question
+// rows' statistics come as nsplit shares, merged here.  LDS: lse2s [G][N_t] row normalisers (base-2 units), and
+// with kl_bytes > 0 the staged pass's area kl (16-byte aligned).
 template <int D>
-__global__ __launch_bounds__(kThreads) void score_text_kernel(Shape s, const uint16_t* __restrict__ q_text,
-                                                              const uint16_t* __restrict__ k,
-                                                              float* __restrict__ lse,
-                                                              float* __restrict__ ws_vm,
-                                                              float* __restrict__ ws_colsum,
-                                                              float* __restrict__ ws_vmh, int lse_given, int hsplit,
-                                                              long long kl_bytes, const float* __restrict__ ws_stat,
-                                                              int nsplit, int one_order) {
-    // [G][N_t] row normalisers, base-2 units; with kl_bytes > 0, then the staged text pass's
-    // LDS (text_pass_lds), 16-byte aligned
-    extern __shared__ float lse2s[];
+__device__ __forceinline__ void text_unit(const Shape& s, int bl, int kvh, int g0, int G,
+                                          const uint16_t* __restrict__ q_text, const uint16_t* __restrict__ k,
+                                          float* __restrict__ lse, float* __restrict__ ws_vm,
+                                          float* __restrict__ ws_colsum, float* __restrict__ ws_vmh, bool lse_given,
+                                          float* lse2s, char* kl, long long kl_bytes, const float* ws_stat, int nsplit,
+                                          int ks, bool one_order) {
     const int tid = threadIdx.x;
-    const int G = s.G / hsplit;  // query heads of this workgroup: g0 .. g0 + G - 1
-    const int g0 = (blockIdx.x % hsplit) * G;
-    const int kvh = blockIdx.x / hsplit % s.Hkv;
-    const int bl = blockIdx.x / hsplit / s.Hkv;
     const size_t head0 = (size_t)bl * s.H + kvh * s.G + g0;
     if (lse_given) {
         // every text row's normaliser comes from the caller (a prefill kernel's row log-sum-exp)
@@ -239,7 +273,7 @@ __global__ __launch_bounds__(kThreads) void score_text_kernel(Shape s, const uin
             float ln;
             if (ws_stat != nullptr) {
                 float vm;
-                merge_row(ws_stat, (size_t)s.B * s.L * s.H * s.Nq, nsplit, (head0 + g) * s.Nq + qi, ln, vm);
+                merge_row(ws_stat, (size_t)s.B * s.L * s.H * s.Nq, nsplit, ks, (head0 + g) * s.Nq + qi, ln, vm);
                 lse[(head0 + g) * s.Nt + s.Ns + qi] = ln;
                 ws_vm[(head0 + g) * s.Nq + qi] = vm;
             } else {
@@ -265,12 +299,30 @@ __global__ __launch_bounds__(kThreads) void score_text_kernel(Shape s, const uin
         }
     }
     __syncthreads();
-    if (kl_bytes > 0) {
-        char* kl = reinterpret_cast<char*>(lse2s) + ((size_t)G * s.Nt * sizeof(float) + 15) / 16 * 16;
-        text_pass_lds<D>(s, bl, kvh, g0, G, q_text, k, lse, lse2s, kl, kl_bytes, ws_colsum, lse_given != 0);
-    } else {
-        text_pass<D>(s, bl, kvh, g0, G, q_text, k, lse, lse2s, ws_colsum, lse_given != 0);
-    }
+    if (kl_bytes > 0)
+        text_pass_lds<D, true>(s, bl, kvh, g0, G, q_text, k, lse, lse2s, kl, kl_bytes, ws_colsum, lse_given);
+    else
+        text_pass<D>(s, bl, kvh, g0, G, q_text, k, lse, lse2s, ws_colsum, lse_given);
+}
+
+// The text pass of one unit, or with hsplit > 1 of one of its query heads (hsplit = G).
+template <int D>
+__global__ __launch_bounds__(kThreads) void score_text_kernel(Shape s, const uint16_t* __restrict__ q_text,
+                                                              const uint16_t* __restrict__ k,
+                                                              float* __restrict__ lse,
+                                                              float* __restrict__ ws_vm,
+                                                              float* __restrict__ ws_colsum,
+                                                              float* __restrict__ ws_vmh, int lse_given, int hsplit,
+                                                              long long kl_bytes, const float* __restrict__ ws_stat,
+                                                              int nsplit, int ks, int one_order) {
+    extern __shared__ float lse2s[];
+    const int G = s.G / hsplit;  // query heads of this workgroup: g0 .. g0 + G - 1
+    const int g0 = (blockIdx.x % hsplit) * G;
+    const int kvh = blockIdx.x / hsplit % s.Hkv;
+    const int bl = blockIdx.x / hsplit / s.Hkv;
+    char* kl = reinterpret_cast<char*>(lse2s) + ((size_t)G * s.Nt * sizeof(float) + 15) / 16 * 16;
+    text_unit<D>(s, bl, kvh, g0, G, q_text, k, lse, ws_vm, ws_colsum, ws_vmh, lse_given != 0, lse2s, kl, kl_bytes, ws_stat,
+                 nsplit, ks, one_order != 0);
 }
 
 // One wave per (unit, query head, 16-key block) of the text->text column sums, when
@@ -572,8 +624,7 @@ RowPlan plan_question_rows(const Shape& s, bool one_order) {
     rp.rowgroups = (NB + 23) / 24;
     rp.ks = 1;
     if (one_order) {
-        // the order of sums that retained sets are taken from stays as it was: 2, 4 or 6 slots,
-        // filled from the first group on
+        // 2, 4 or 6 slots, filled from the first group on: the order of sums that retained sets are taken from
         rp.nslot = NB <= 8 ? 2 : NB <= 16 ? 4 : 6;
         return rp;
     }
@@ -581,59 +632,91 @@ RowPlan plan_question_rows(const Shape& s, bool one_order) {
     return rp;
 }
 
-// Shares of a unit's keys that the statistics sweep is split over.  One workgroup per (unit, row
-// group) leaves the chip idle when there are few of them; the split fills one round of resident
-// workgroups (4, 3, 2, 2 per CU at 1, 2, 4, 6 row slots), each share at least kMinShareTiles key
-// tiles.  It costs the separate text pass, so it is only taken from 12 key tiles on, or from 6 when
-// four or more row slots make each tile long.  Statistics and text, one layer: 32 units of 64
-// question rows, 447 keys 15.5 us whole against 17.0 split, 699 keys 21.0 against 18.5, 2979 keys
-// about 50 against 21; 16 units of 336 rows, 464 keys 41.7 against 28.3.  112 units of 336 rows
-// over 8256 keys: 288 us whole, 124 split.  Shares of 3 tiles against 4: 17.3 against 20.9 us in
-// the sweep at 4 units, 1-2 us shorter at 32.
-// With one or two row slots a sweep is a stream of keys and a workgroup on every second CU already
-// draws much of the bandwidth, so it is split up to 128 units only, and the more units the longer
-// they have to be: 128 units of 2979 keys 47.6 us whole against 37.0 split, of 1221 keys 21.2 against
-// 23.3, 64 units of 1221 keys 20.9 against 19.6; 256 units of 1221 keys 25.0 us
-// whole against 31.1 split, 480 units of 2979 keys 76.6 against 82.4 (six slots: 224 units of 1583
-// keys 92.5 against 75.9, 4078 keys 127.7 against 108.0).
-constexpr int kMinShareTiles = 3;
+// Key tiles per share: a unit's row statistics are summed share by share, each share afresh, and the shares
+// added in order (merge_shares).  The shares follow from the sequence's own shape, never from the batch, so
+// that a sequence gets the same bits in any batch; whether they are dealt to workgroups of their own
+// (stats_spread) is then free.  Without them one workgroup per (unit, row group) leaves most of the chip idle
+// where units are few: one video of 28 layers has 112, whose statistics and text took 299 us against 123.
+//
+// Shares for a single sequence to fill one round of resident workgroups (4, 3, 3, 2 per CU at 1, 2, 3, 4 and more row
+// slots), of four key tiles or more, in rows of 12 key tiles or more (6 where four slots or more make
+// each tile long and units are few).  Statistics and text, microseconds, whole / in shares: one layer of 32
+// units of 64 question rows, 1599 keys 31.9 / 22.4; of 4085 keys 57 / 26; one layer of 8 units of 200 rows, 4085 keys
+// 115 / 28; of 4 units of 336 rows, 8275 keys 294 / 39.  A sweep of one or two slots is a stream of
+// keys, and half the CUs already draw much of the bandwidth: only sequences of up to 128 units, and the
+// more units the longer.  Three and four slots give up their fused text pass for the shares
+// (stats_text_eligible), which costs large batches up to a tenth (512 units of 200 rows, 1599 keys: 100 / 109), so they
+// have the same limit.
+constexpr int kMinShareTiles = 4;
 constexpr int kMaxShares = 32;
 constexpr int kLightUnits = 128;
 
-int stats_splits(const Shape& s, const RowPlan& rp) {
-    const long long units = (long long)s.B * s.L * s.Hkv * rp.rowgroups;
+int share_tiles(const Shape& s, const RowPlan& rp) {
     const int tiles = (s.N + kTile - 1) / kTile;
-    if (rp.one_order || units <= 0 || tiles < (rp.nslot >= 4 ? 6 : 12)) return 1;
-    if (rp.nslot <= 2 && rp.rowgroups == 1 && (units > kLightUnits || units > 5LL * tiles * rp.nslot)) return 1;
+    const long long units = (long long)s.L * s.Hkv * rp.rowgroups;  // of one sequence
+    if (rp.one_order || units <= 0 || tiles < (rp.nslot <= 2 || units > kLightUnits / 2 ? 12 : 6)) return tiles;
+    if (rp.rowgroups == 1 && rp.nslot <= 4 && units > kLightUnits) return tiles;
+    if (rp.rowgroups == 1 && rp.nslot <= 2 && units > 5LL * tiles * rp.nslot) return tiles;
     const int per_cu = rp.nslot == 1 ? 4 : rp.nslot <= 3 ? 3 : 2;
     const int n = (int)std::min<long long>(std::min<long long>(256 * per_cu / units, tiles / kMinShareTiles), kMaxShares);
-    if (n <= 1) return 1;
-    const int per = (tiles + n - 1) / n;  // tiles per share; no share is empty
+    if (n <= 1) return tiles;
+    const int per = (tiles + n - 1) / n;  // the last share takes what remains
+    return rp.nslot <= 2 ? (per + 1) / 2 * 2 : per;  // an even number with two tiles in flight (stats_sweep)
+}
+
+int stats_splits(const Shape& s, const RowPlan& rp) {
+    const int tiles = (s.N + kTile - 1) / kTile, per = share_tiles(s, rp);
     return (tiles + per - 1) / per;
+}
+
+// Whether the shares go to workgroups of their own, and the text pass merges them; else a workgroup sweeps a
+// unit's shares one after another.  Up to 256 units, one per CU (224 of six slots and 8256 keys take 317 us
+// in one workgroup each, 240 spread; 448 units 409 and 426); one- and two-slot sweeps up to 128, or
+// more the longer they are (128 units of 1599 keys 33.6 and 30.5, 256 units 35.8 and 38.2; 256 units of 8275 keys 115 and
+// 107, 512 units 186 and 193).
+bool stats_spread(const Shape& s, const RowPlan& rp) {
+    if (stats_splits(s, rp) == 1) return false;
+    const long long units = (long long)s.B * s.L * s.Hkv * rp.rowgroups;
+    const int tiles = (s.N + kTile - 1) / kTile;
+    if (rp.nslot <= 2 && rp.rowgroups == 1) return units <= std::max(128, std::min(4 * tiles * rp.nslot, 384));
+    return units <= 256;
 }
 
 hipError_t launch_score_stats(const Shape& s, const RowPlan& rp, const uint16_t* q_text, const uint16_t* k,
                               float* lse, float* ws_vm, float* ws_stat, bool merge, hipStream_t st) {
-    const int nsplit = stats_splits(s, rp);
+    const int nsplit = stats_spread(s, rp) ? stats_splits(s, rp) : 1;
+    const bool shares = nsplit == 1 && stats_splits(s, rp) > 1;  // one after another in one workgroup
     const long long nblk = (long long)s.B * s.L * s.Hkv * rp.rowgroups * nsplit;
     if (nblk == 0) return hipSuccess;
     dim3 grid((unsigned)nblk), block(kThreads);
-    if (s.D == 128)
-        TGVKV_ROWPLAN_DISPATCH(score_stats_kernel, 128, rp, grid, block, 0, st, s, rp.rowgroups, q_text, k, lse, ws_vm, nsplit, ws_stat);
-    else
-        TGVKV_ROWPLAN_DISPATCH(score_stats_kernel, 64, rp, grid, block, 0, st, s, rp.rowgroups, q_text, k, lse, ws_vm, nsplit, ws_stat);
+    const int per = share_tiles(s, rp);
+    auto launch = [&](auto d) {
+        constexpr int D = decltype(d)::value;
+        if (shares)
+            TGVKV_ROWPLAN_DISPATCH_M(score_stats_kernel, D, true, rp, grid, block, 0, st, s, rp.rowgroups, q_text, k, lse, ws_vm, nsplit, per, ws_stat);
+        else
+            TGVKV_ROWPLAN_DISPATCH_M(score_stats_kernel, D, false, rp, grid, block, 0, st, s, rp.rowgroups, q_text, k, lse, ws_vm, nsplit, per, ws_stat);
+    };
+    if (s.D == 128) launch(IC<128>{});
+    else launch(IC<64>{});
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || nsplit == 1 || !merge) return e;
     const long long rows = (long long)s.B * s.L * s.H * s.Nq;
     hipLaunchKernelGGL(score_stats_merge_kernel, dim3((unsigned)((rows + kThreads - 1) / kThreads)), block, 0, st, s,
-                       ws_stat, nsplit, lse, ws_vm);
+                       ws_stat, nsplit, rp.ks, lse, ws_vm);
     return hipGetLastError();
 }
 
 bool stats_text_eligible(const Shape& s, const RowPlan& rp) {
-    if (rp.rowgroups != 1 || s.Nt == 0 || stats_splits(s, rp) > 1) return false;
-    const long long floats = (long long)s.G * (s.Nt + s.Nq);
+    if (rp.rowgroups != 1 || s.Nt == 0 || stats_spread(s, rp)) return false;
     const long long tile_bytes = 2LL * kTile * (2 * s.D + 16);
+    if (stats_splits(s, rp) > 1) {
+        if (rp.nslot == 3 || rp.nslot == 4) return false;  // the text pass is the staged one (launch_score_text stages these too)
+        const long long head = ((long long)s.G * (s.Nt + s.Nq) * 4 + 15) / 16 * 16;
+        return s.D == 128 ? text_lds_fits<128>(s.G, s.Ns, s.Nt, tile_bytes - head)
+                          : text_lds_fits<64>(s.G, s.Ns, s.Nt, tile_bytes - head);
+    }
+    const long long floats = (long long)s.G * (s.Nt + s.Nq);
     return floats * 4 <= tile_bytes;
 }
 
@@ -642,6 +725,24 @@ hipError_t launch_score_stats_text(const Shape& s, const RowPlan& rp, const uint
     const long long nblk = (long long)s.B * s.L * s.Hkv;
     if (nblk == 0) return hipSuccess;
     dim3 grid((unsigned)nblk), block(kThreads);
+    if (stats_splits(s, rp) > 1) {
+        const int per = share_tiles(s, rp);
+        auto launch = [&](auto d) {
+            constexpr int D = decltype(d)::value;
+            auto go = [&](auto kernel) {
+                hipLaunchKernelGGL(kernel, grid, block, 0, st, s, q_text, k, lse, ws_vm, ws_colsum, ws_vmh, 1, per);
+            };
+            if (rp.ks == 4) go(score_stats_text_kernel<D, 1, 4, false, true>);
+            else if (rp.ks == 2) go(score_stats_text_kernel<D, 1, 2, false, true>);
+            else if (rp.nslot == 1) go(score_stats_text_kernel<D, 1, 1, false, true>);
+            else if (rp.nslot == 2) go(score_stats_text_kernel<D, 2, 1, false, true>);
+            else if (rp.nslot == 5) go(score_stats_text_kernel<D, 5, 1, false, true>);
+            else go(score_stats_text_kernel<D, 6, 1, false, true>);
+        };
+        if (s.D == 128) launch(IC<128>{});
+        else launch(IC<64>{});
+        return hipGetLastError();
+    }
     // Text mode 2 (the question rows' fragments reused from the sweep, the system keys staged
     // in the tiles, the question keys streamed through them) needs the normalisers, masses and
     // column partials in a dynamic LDS area that leaves the kernel's occupancy as it is.
@@ -656,7 +757,7 @@ hipError_t launch_score_stats_text(const Shape& s, const RowPlan& rp, const uint
     if (qregs) {
         auto launch = [&](auto d, auto ns) {
             hipLaunchKernelGGL((score_stats_text_kernel<decltype(d)::value, decltype(ns)::value, 1, true>), grid, block,
-                               (size_t)area, st, s, q_text, k, lse, ws_vm, ws_colsum, ws_vmh, 2);
+                               (size_t)area, st, s, q_text, k, lse, ws_vm, ws_colsum, ws_vmh, 2, 0);
         };
         if (s.D == 128 && rp.nslot == 3) launch(IC<128>{}, IC<3>{});
         else if (s.D == 128) launch(IC<128>{}, IC<4>{});
@@ -667,11 +768,11 @@ hipError_t launch_score_stats_text(const Shape& s, const RowPlan& rp, const uint
     if (s.D == 128) {
         const int mode = text_lds_fits<128>(s.G, s.Ns, s.Nt, tile_bytes - head) ? 1 : 0;
         TGVKV_ROWPLAN_DISPATCH(score_stats_text_kernel, 128, rp, grid, block, 0, st, s, q_text, k, lse, ws_vm,
-                               ws_colsum, ws_vmh, mode);
+                               ws_colsum, ws_vmh, mode, 0);
     } else {
         const int mode = text_lds_fits<64>(s.G, s.Ns, s.Nt, tile_bytes - head) ? 1 : 0;
         TGVKV_ROWPLAN_DISPATCH(score_stats_text_kernel, 64, rp, grid, block, 0, st, s, q_text, k, lse, ws_vm,
-                               ws_colsum, ws_vmh, mode);
+                               ws_colsum, ws_vmh, mode, 0);
     }
     return hipGetLastError();
 }
@@ -681,10 +782,6 @@ hipError_t launch_score_text(const Shape& s, const RowPlan& rp, const uint16_t* 
                              hipStream_t st) {
     const long long nblk = (long long)s.B * s.L * s.Hkv;
     if (nblk == 0 || s.Nt == 0) return hipSuccess;
-    // with few units, one workgroup per query head: each stages the unit's text keys again (from
-    // cache), but a unit's heads no longer follow one another in the same four waves
-    const int hsplit = s.G > 1 && nblk <= kHeadSplitUnits && !rp.one_order ? s.G : 1;
-    const int G = s.G / hsplit;
     // the unit's text keys staged in LDS (text_pass_lds; in chunks of key blocks when they do not
     // all fit beside the normalisers): against one wave per (unit, head, 16-key block) walking the row
     // blocks from global memory, at llavanext 80 -> 20 us.  Within 40 KB, four workgroups per CU, when
@@ -692,24 +789,30 @@ hipError_t launch_score_text(const Shape& s, const RowPlan& rp, const uint16_t* 
     // rows took 85 us in one chunk with two workgroups per CU, 60 us in two chunks with four (224 units
     // of 7 heads); 130 rows 47 and 43 us.
     const int TB = (s.Nt + 15) / 16;
-    const long long head = ((long long)G * s.Nt * 4 + 15) / 16 * 16;
     const int sys = lse_given ? 0 : s.Ns;
-    long long kl = 0;  // 0: not staged
-    auto fit = [&](auto d) {
+    auto head_bytes = [&](int G) { return ((long long)G * s.Nt * 4 + 15) / 16 * 16; };
+    auto fit = [&](auto d, int G) -> long long {  // bytes of the staged pass for G heads; 0: not staged
         constexpr int D = decltype(d)::value;
         for (const long long cap : {40960LL, 65536LL}) {
-            const long long k = std::min<long long>(text_part_bytes<D>(G, s.Nt) + 16LL * TB * Geo<D>::ROWB, cap - head);
+            const long long k = std::min<long long>(text_part_bytes<D>(G, s.Nt) + 16LL * TB * Geo<D>::ROWB, cap - head_bytes(G));
             if (k > 0 && text_lds_fits<D>(G, sys, s.Nt, k) &&
-                (cap == 65536LL || text_chunk_blocks<D>(G, s.Nt, k) >= std::min(TB, 6))) {
-                kl = k;
-                return;
-            }
+                (cap == 65536LL || text_chunk_blocks<D>(G, s.Nt, k) >= std::min(TB, 6)))
+                return k;
         }
+        return 0;
     };
-    if (!rp.one_order) {
-        if (s.D == 128) fit(IC<128>{});
-        else fit(IC<64>{});
+    auto staged_bytes = [&](int G) { return rp.one_order ? 0LL : s.D == 128 ? fit(IC<128>{}, G) : fit(IC<64>{}, G); };
+    // With few units, one workgroup per query head: each stages the unit's text keys again (from
+    // cache), but a unit's heads no longer follow one another in the same four waves; also where only one
+    // head's partials leave room for the keys (the sums have one order either way, staged or not)
+    long long kl = staged_bytes(s.G);
+    int hsplit = 1;
+    if (s.G > 1 && !rp.one_order && (nblk <= kHeadSplitUnits || kl == 0)) {
+        hsplit = s.G;
+        kl = staged_bytes(1);
     }
+    const int G = s.G / hsplit;
+    const long long head = head_bytes(G);
     const bool staged = kl > 0;
     if (lse_given && !staged) {
         const long long items = nblk * s.G * TB;
@@ -723,13 +826,14 @@ hipError_t launch_score_text(const Shape& s, const RowPlan& rp, const uint16_t* 
     }
     dim3 grid((unsigned)(nblk * hsplit)), block(kThreads);
     const size_t lds = staged ? (size_t)(head + kl) : sizeof(float) * (size_t)G * s.Nt;
-    const int nsplit = ws_stat != nullptr ? stats_splits(s, rp) : 1;
+    const int nsplit = stats_spread(s, rp) ? stats_splits(s, rp) : 1;
+    if (nsplit == 1) ws_stat = nullptr;
     if (s.D == 128)
         hipLaunchKernelGGL(score_text_kernel<128>, grid, block, lds, st, s, q_text, k, lse, ws_vm, ws_colsum, ws_vmh,
-                           (int)lse_given, hsplit, kl, ws_stat, nsplit, (int)rp.one_order);
+                           (int)lse_given, hsplit, kl, ws_stat, nsplit, rp.ks, (int)rp.one_order);
     else
         hipLaunchKernelGGL(score_text_kernel<64>, grid, block, lds, st, s, q_text, k, lse, ws_vm, ws_colsum, ws_vmh,
-                           (int)lse_given, hsplit, kl, ws_stat, nsplit, (int)rp.one_order);
+                           (int)lse_given, hsplit, kl, ws_stat, nsplit, rp.ks, (int)rp.one_order);
     return hipGetLastError();
 }
 

@@ -215,13 +215,16 @@ __device__ __forceinline__ void load_qrows(const Shape& s, const uint16_t* q_tex
 // per question row a reference max m (base-2 units, within 8 of the row's largest
 // logit), the sum of exp2(z - m) over visible keys and the same sum over vision
 // keys, so that m + log2(sum) is the row's normaliser.  On return the key-part-0
-// waves hold, in lanes 0..15, the merged statistics of their rows; the workgroup
-// is synced.
-template <int D, int NSLOT, int KS>
+// waves hold, in lanes 0..15, the merged statistics of their rows (with key_parts
+// each wave holds its own key part's); the workgroup is synced.
+// SHARES: every share_tiles tiles (an even number) start afresh, and the shares' statistics are
+// added in share order: the same bits as the sweeps of the shares one by one, merged so,
+// but with the tile pipeline running on.
+template <int D, int NSLOT, int KS, bool SHARES = false>
 __device__ void stats_sweep(const Shape& s, const uint16_t* kbase, int kbeg, int kend,
                             const bf16x8 (&qf)[NSLOT][Geo<D>::KSTEPS], const int (&qrow)[NSLOT],
                             char (*tiles)[Geo<D>::TILE_BYTES], float (&m)[NSLOT], float (&lsum)[NSLOT],
-                            float (&vsum)[NSLOT]) {
+                            float (&vsum)[NSLOT], int share_tiles = 0, bool key_parts = false) {
     using GG = Geo<D>;
     constexpr int RSETS = 4 / KS;
     constexpr int KBW = 4 / KS;
@@ -328,23 +331,58 @@ __device__ void stats_sweep(const Shape& s, const uint16_t* kbase, int kbeg, int
     // tiles [t0, t1) lie wholly inside the vision keys (and below kend): they skip the masks
     const int t0 = vis0 > kbeg ? (vis0 - kbeg + kTile - 1) / kTile : 0;
     const int t1 = max((min(vis1, kend) - kbeg) / kTile, t0);
+    // the four lane quarters of a wave saw different keys of the same rows
+    auto merge_quarters = [&]() {
+#pragma unroll
+        for (int sl = 0; sl < NSLOT; ++sl) lsum[sl] = tsum[sl] + vsum[sl];
+#pragma unroll
+        for (int sl = 0; sl < NSLOT; ++sl) {
+#pragma unroll
+            for (int off = 16; off < 64; off <<= 1) {
+                const float m2 = shfl_xor(m[sl], off), l2 = shfl_xor(lsum[sl], off), v2 = shfl_xor(vsum[sl], off);
+                merge_stats(m[sl], lsum[sl], vsum[sl], m2, l2, v2);
+            }
+        }
+    };
+    // SHARES: the shares' statistics, added in share order
+    float sm[SHARES ? NSLOT : 1], sl_[SHARES ? NSLOT : 1], sv[SHARES ? NSLOT : 1];
+    int next = share_tiles - 1;  // the share's last tile
+    auto end_share = [&]() {
+        merge_quarters();
+#pragma unroll
+        for (int sl = 0; sl < NSLOT; ++sl) {
+            if (next == share_tiles - 1) {
+                sm[sl] = m[sl];
+                sl_[sl] = lsum[sl];
+                sv[sl] = vsum[sl];
+            } else {
+                merge_shares(sm[sl], sl_[sl], sv[sl], m[sl], lsum[sl], vsum[sl]);
+            }
+            m[sl] = kNegInf;
+            tsum[sl] = 0.f;
+            vsum[sl] = 0.f;
+        }
+        next += share_tiles;
+    };
     tile_pipeline_phased<D, PipeDepth<NSLOT>::value>(
         kbase, kbeg, kend, tiles, t0, t1,
         [&](const char* buf, int key0, int) { tile(buf, key0, std::false_type{}); },
         [&](const char* buf, int key0, int) { tile(buf, key0, std::true_type{}); },
-        [](int, int) {});
+        [&](int, int t) {
+            if (SHARES && t == next && kbeg + (t + 1) * kTile < kend) end_share();
+        });
+    if constexpr (SHARES) {
+        end_share();
 #pragma unroll
-    for (int sl = 0; sl < NSLOT; ++sl) lsum[sl] = tsum[sl] + vsum[sl];
-    // the four lane quarters of a wave saw different keys of the same rows
-#pragma unroll
-    for (int sl = 0; sl < NSLOT; ++sl) {
-#pragma unroll
-        for (int off = 16; off < 64; off <<= 1) {
-            const float m2 = shfl_xor(m[sl], off), l2 = shfl_xor(lsum[sl], off), v2 = shfl_xor(vsum[sl], off);
-            merge_stats(m[sl], lsum[sl], vsum[sl], m2, l2, v2);
+        for (int sl = 0; sl < NSLOT; ++sl) {
+            m[sl] = sm[sl];
+            lsum[sl] = sl_[sl];
+            vsum[sl] = sv[sl];
         }
+    } else {
+        merge_quarters();
     }
-    if (KS > 1) {
+    if (KS > 1 && !key_parts) {
         // waves of other key parts hand their partials to the key-part-0 wave of their row set
         float* red = reinterpret_cast<float*>(tiles[0]);  // [wave][NSLOT][16][3]
         if (kp > 0 && lane < 16) {
@@ -363,7 +401,8 @@ __device__ void stats_sweep(const Shape& s, const uint16_t* kbase, int kbeg, int
 #pragma unroll
                 for (int sl = 0; sl < NSLOT; ++sl) {
                     const float* r = red + ((w2 * NSLOT + sl) * 16 + lane) * 3;
-                    merge_stats(m[sl], lsum[sl], vsum[sl], r[0], r[1], r[2]);
+                    if (SHARES) merge_shares(m[sl], lsum[sl], vsum[sl], r[0], r[1], r[2]);
+                    else merge_stats(m[sl], lsum[sl], vsum[sl], r[0], r[1], r[2]);
                 }
             }
         }
@@ -681,7 +720,10 @@ __host__ __device__ constexpr bool text_lds_fits(int G, int Ns, int Nt, long lon
 // normalisers (the question rows' on entry; every row's with lse_given, and then the
 // system rows' are not computed and lse is not written); kl points at kl_bytes of 16-byte
 // aligned LDS with text_lds_fits<D>(G, N_s, N_t, kl_bytes).
-template <int D>
+// BY_ROW: wave w of head g owns the row blocks rb with (rb + g) % 4 == w, so the order of a column's sum
+// depends on neither the heads of the workgroup nor the chunks.  Otherwise the (head, row block) items
+// are dealt to the waves in turn.
+template <int D, bool BY_ROW = false>
 __device__ void text_pass_lds(const Shape& s, int bl, int kvh, int g0, int G, const uint16_t* __restrict__ q_text,
                               const uint16_t* __restrict__ k, float* __restrict__ lse, float* lse2s, char* kl,
                               long long kl_bytes, float* __restrict__ ws_colsum, bool lse_given = false) {
@@ -706,8 +748,21 @@ __device__ void text_pass_lds(const Shape& s, int bl, int kvh, int g0, int G, co
         const int it = min(item, G * SB - 1);
         load_q(f, it / SB, min((it % SB) * 16 + (lane & 15), s.Ns - 1));
     };
-    // column items of a chunk starting at key block c0: row blocks rb >= c0 of every head
+    // column items of a chunk starting at key block c0: row blocks rb >= c0 of every head.  BY_ROW: a wave's
+    // item `item` is its own and names head item / per and that head's next row block (past the last: nothing)
+    auto row_item = [&](int item, int c0, int& g, int& rb) {
+        const int per = (TB - c0 + 3) >> 2;
+        g = min(item / per, G - 1);
+        rb = c0 + 4 * (item % per) + ((wave - g0 - g - c0) & 3);
+        return item < G * per && rb < TB;
+    };
     auto col_item_q = [&](bf16x8 (&f)[GG::KSTEPS], int item, int c0) {
+        if constexpr (BY_ROW) {
+            int g, rb;
+            row_item(item, c0, g, rb);
+            load_q(f, g, min(rb * 16 + (lane & 15), s.Nt - 1));
+            return;
+        }
         const int nrb = TB - c0;
         const int it = min(item, G * nrb - 1);
         load_q(f, it / nrb, min((c0 + it % nrb) * 16 + (lane & 15), s.Nt - 1));
@@ -730,7 +785,7 @@ __device__ void text_pass_lds(const Shape& s, int bl, int kvh, int g0, int G, co
             }
             if (x0 == 0) {
                 if (c0 == 0 && SB > 0) sys_item_q(qs, wave);
-                col_item_q(qa, wave, c0);
+                col_item_q(qa, BY_ROW ? 0 : wave, c0);
             }
 #pragma unroll
             for (int i = 0; i < kStage; ++i) {
@@ -797,7 +852,12 @@ __device__ void text_pass_lds(const Shape& s, int bl, int kvh, int g0, int G, co
         const int nrb = TB - c0;
         const int items = G * nrb;
         auto consume = [&](const bf16x8 (&qf)[GG::KSTEPS], int item) {
-            const int g = item / nrb, rb = c0 + item % nrb;
+            int g, rb;
+            if constexpr (BY_ROW) {
+                if (!row_item(item, c0, g, rb)) return;
+            } else {
+                g = item / nrb, rb = c0 + item % nrb;
+            }
             float* wpart = part + ((size_t)wave * G + g) * TK;
             float l2[4];
 #pragma unroll
@@ -823,15 +883,16 @@ __device__ void text_pass_lds(const Shape& s, int bl, int kvh, int g0, int G, co
         };
         // this wave's items are wave, wave + 4, ...: two register sets, the next item's
         // fragments fetched while the current one is used (qa already holds the first)
-        const int steps = (items + 3) / 4;
-        int item = wave;
+        const int steps = BY_ROW ? G * ((nrb + 3) >> 2) : (items + 3) / 4;
+        const int step = BY_ROW ? 1 : 4;
+        int item = BY_ROW ? 0 : wave;
         for (int st = 0; st < steps; st += 2) {
-            const int nx = item + 4;
+            const int nx = item + step;
             col_item_q(qb, nx, c0);
-            if (item < items) consume(qa, item);
-            const int nx2 = item + 8;
+            if (BY_ROW || item < items) consume(qa, item);
+            const int nx2 = item + 2 * step;
             col_item_q(qa, nx2, c0);
-            if (nx < items) consume(qb, nx);
+            if (BY_ROW || nx < items) consume(qb, nx);
             item = nx2;
         }
         __syncthreads();  // the chunk's keys are done with before the next is staged

@@ -145,6 +145,17 @@ __device__ __forceinline__ void merge_stats(float& m, float& l, float& v, float 
     m = mn;
 }
 
+// merge_stats with its products and sums spelled out: the same bits in every kernel it is compiled into (which of
+// the two products the compiler contracts is its choice otherwise).
+__device__ __forceinline__ void merge_shares(float& m, float& l, float& v, float m2, float l2, float v2) {
+    const float mn = fmaxf(m, m2);
+    const float mu = mn == kNegInf ? 0.f : mn;  // no visible key on either side: sums of 0
+    const float s1 = fast_exp2(m - mu), s2 = fast_exp2(m2 - mu);
+    l = __builtin_fmaf(l, s1, l2 * s2);
+    v = __builtin_fmaf(v, s1, v2 * s2);
+    m = mn;
+}
+
 // Map a float to an unsigned key with the same order (-0.0 treated as +0.0).
 __device__ __forceinline__ uint32_t ordered_key(float f) {
     uint32_t b = __float_as_uint(f);

@@ -23,14 +23,16 @@ struct Shape {
 // (each up to NSLOT blocks) and, for few blocks, split each key tile into KS parts.
 struct RowPlan {
     int nslot, ks, rowgroups;
-    bool one_order;  // sums in an order set by the unit's shape alone (TGVKV_SCORE_ONE_ORDER)
+    bool one_order;  // a unit's keys summed in one run (TGVKV_SCORE_ONE_ORDER)
 };
 
 RowPlan plan_question_rows(const Shape& s, bool one_order);
 
-// Score phases.  ws_stat: the statistics of a sweep whose keys are split ([3][splits][B*L*H][N_q],
-// unused without a split); merge: turn them into lse and ws_vm here, else the text pass does.
+// Score phases.  A unit's statistics are summed in stats_splits shares of its keys; with stats_spread each
+// share has a workgroup of its own and leaves its statistics in ws_stat ([3][key parts][splits][B*L*H][N_q]);
+// merge: turn them into lse and ws_vm here, else the text pass does.
 int stats_splits(const Shape& s, const RowPlan& rp);
+bool stats_spread(const Shape& s, const RowPlan& rp);
 hipError_t launch_score_stats(const Shape& s, const RowPlan& rp, const uint16_t* q_text, const uint16_t* k,
                               float* lse, float* ws_vm, float* ws_stat, bool merge, hipStream_t st);
 bool stats_text_eligible(const Shape& s, const RowPlan& rp);

@@ -113,8 +113,8 @@ def test_row_plans(lib, blocks, head_dim):
 
 
 def test_one_order_in_any_batch(lib):
-    """With ONE_ORDER a sequence's scores are the same bits alone, where other calls split its keys over workgroups,
-    and in a batch; with given normalisers the flag is refused."""
+    """With ONE_ORDER a sequence's scores are the same bits alone and in a batch; with given normalisers the flag is
+    refused."""
     import torch
     log("one order")
     shape = dict(layers=3, heads_q=14, heads_kv=2, n_sys=9, n_vis=900, n_qst=60)
@@ -131,6 +131,60 @@ def test_one_order_in_any_batch(lib):
         assert torch.equal(a[0], b[0]) and torch.equal(b[0], b[78]) and torch.equal(b[1], b[79]), n
     with pytest.raises(bd.TgvkvError):
         one.score(q[:1], k[:1], bd.SCORE_TEXT | bd.SCORE_VISION | bd.SCORE_LSE_IN | bd.SCORE_ONE_ORDER)
+
+
+# one sequence of each row plan: its key parts, slots and row groups, text passes staged whole, in chunks and not at all
+SEQUENCES = {
+    "one_block": dict(heads_q=2, heads_kv=2, n_sys=35, n_vis=1501, n_qst=16),
+    "two_blocks": dict(heads_q=2, heads_kv=2, n_sys=0, n_vis=2002, n_qst=30),
+    "three_blocks_d64": dict(heads_q=2, heads_kv=2, head_dim=64, n_sys=70, n_vis=1700, n_qst=45),
+    "one_slot": dict(heads_q=2, heads_kv=2, n_sys=130, n_vis=1500, n_qst=64),
+    "two_slots": dict(heads_q=4, heads_kv=2, n_sys=9, n_vis=1333, n_qst=50),
+    "three_slots": dict(heads_q=2, heads_kv=2, n_sys=20, n_vis=1100, n_qst=180),
+    "four_slots_d64": dict(heads_q=8, heads_kv=2, head_dim=64, n_sys=20, n_vis=1100, n_qst=60),
+    "five_slots": dict(heads_q=10, heads_kv=2, n_sys=5, n_vis=1250, n_qst=60),
+    "six_slots": dict(heads_q=14, heads_kv=2, n_sys=16, n_vis=1300, n_qst=40),
+    "six_slots_d64": dict(heads_q=14, heads_kv=2, head_dim=64, n_sys=100, n_vis=1300, n_qst=48),
+    "row_groups": dict(heads_q=14, heads_kv=2, n_sys=3, n_vis=1100, n_qst=60),
+    "long_text": dict(heads_q=14, heads_kv=2, n_sys=260, n_vis=700, n_qst=160),
+    "unstaged_text": dict(heads_q=4, heads_kv=2, n_sys=3000, n_vis=600, n_qst=30),
+    "short": dict(heads_q=4, heads_kv=2, n_sys=5, n_vis=300, n_qst=20),
+}
+
+
+@pytest.mark.parametrize("name", sorted(SEQUENCES))
+def test_same_bits_in_any_batch(lib, name):
+    """A sequence's scores are the same bits in a batch of any size, however the call is made: alone, where its keys are
+    spread over workgroups, and where a workgroup takes a unit's keys whole, with more units than get a text workgroup
+    per query head.  With given normalisers the layers' masses are sums over the batch's shares, and may differ."""
+    import torch
+    log(f"same bits in any batch {name}")
+    shape = dict(dict(layers=1), **SEQUENCES[name])
+    t = make_prefill_tensors(custom_config(batch=2, **shape), seed=2, names=("q_text", "k"))
+    q, k = (dev_bf16(t[n]) for n in ("q_text", "k"))
+    lse = torch.randn(2, 1, shape["heads_q"], shape["n_sys"] + shape["n_qst"], device="cuda").abs() + 7
+    names = ("lse", "s_txt", "w_txt", "tv_mass", "s_vis")
+    ways = {"all": (bd.SCORE_ALL,), "two": (bd.SCORE_STATS | bd.SCORE_TEXT, bd.SCORE_VISION),
+            "phases": (bd.SCORE_STATS, bd.SCORE_TEXT, bd.SCORE_VISION), "one order": (bd.SCORE_ALL | bd.SCORE_ONE_ORDER,),
+            "lse": (bd.SCORE_TEXT | bd.SCORE_VISION | bd.SCORE_LSE_IN,)}
+    for way, phases in ways.items():
+        first = None
+        for batch in (1, 2, 40, 100, 150, 200, 260):
+            order = torch.arange(batch, device="cuda") % 2
+            buf = bd.EvictionBuffers(bd.problem_from(custom_config(batch=batch, **shape)), None, 0, 1)
+            buf.ws_score.fill_(255)
+            buf.lse.copy_(lse[order])
+            for ph in phases:
+                buf.score(q[order].contiguous(), k[order].contiguous(), ph)
+            got = {n: getattr(buf, n).clone() for n in names if not (way == "lse" and n == "tv_mass")}
+            if batch == 2:
+                first = got
+            elif batch == 1:
+                alone = got
+            for n, x in got.items():
+                assert torch.isfinite(x).all(), (way, batch, n)
+                assert torch.equal(x[0], alone[n][0]), (way, batch, n)
+                assert first is None or torch.equal(x, first[n][order]), (way, batch, n)
 
 
 # positions per row: each count of waves and register groups to its last position, the first past it, and past them all
