@@ -598,8 +598,11 @@ int resident_workgroups(const void* kernel, size_t dyn_lds) {
 }  // namespace
 
 // Units (KV heads of all sequences and layers) up to which the text pass runs one workgroup per
-// query head.
-constexpr long long kHeadSplitUnits = 512;
+// query head: one unit per CU, or twice as many from 12 blocks of text rows on.  Scoring with given normalisers,
+// split / whole: 7 heads, 55 text rows, 336 units 109 / 102 us, 448 units 130 / 119; 83 rows, 448 units 172 / 165;
+// 235 rows, 336 units 427 / 442, 448 units 529 / 525; 8 heads, 235 rows, 320 units 367 / 397.  256 units of
+// 8 heads, split, against the whole pass as it was: 82 / 107 (83 rows).
+long long head_split_units(const Shape& s) { return (s.Nt + 15) / 16 >= 12 ? 512 : 256; }
 
 RowPlan plan_question_rows(const Shape& s, bool one_order) {
     const int QB = (s.Nq + 15) / 16;
@@ -807,7 +810,7 @@ hipError_t launch_score_text(const Shape& s, const RowPlan& rp, const uint16_t* 
     // head's partials leave room for the keys (the sums have one order either way, staged or not)
     long long kl = staged_bytes(s.G);
     int hsplit = 1;
-    if (s.G > 1 && !rp.one_order && (nblk <= kHeadSplitUnits || kl == 0)) {
+    if (s.G > 1 && !rp.one_order && (nblk <= head_split_units(s) || kl == 0)) {
         hsplit = s.G;
         kl = staged_bytes(1);
     }
