@@ -47,7 +47,7 @@
 extern "C" {
 #endif
 
-#define TGVKV_ABI_VERSION 8
+#define TGVKV_ABI_VERSION 9
 
 typedef enum tgvkv_status {
     TGVKV_OK = 0,

@@ -24,7 +24,7 @@ SCORE_LSE_IN = 16  # lse holds the text rows' normalisers from the caller's pref
 SCORE_ONE_ORDER = 32  # with any phases: every unit's keys summed in one run, not in shares
 CALL_SCORE, CALL_DECODE = 0, 1
 
-ABI_VERSION = 8  # TGVKV_ABI_VERSION of the library this binding marshals for
+ABI_VERSION = 9  # TGVKV_ABI_VERSION of the library this binding marshals for
 EXPORTS = ("tgvkv_score", "tgvkv_budget", "tgvkv_select", "tgvkv_compact", "tgvkv_decode_attn",
            "tgvkv_decode_attn_noalloc",
            "tgvkv_page_plan", "tgvkv_page_table", "tgvkv_compact_paged", "tgvkv_decode_attn_paged",

@@ -9,6 +9,7 @@ reach a kernel launch on real hardware.
 import ctypes
 import os
 import re
+import subprocess
 
 import pytest
 
@@ -49,7 +50,7 @@ def test_exports_every_declared_symbol(lib):
     assert sorted(ceiling) == sorted(bd.CEILING_EXPORTS), ceiling
     for n in names + ceiling:
         assert hasattr(lib, n), n
-    assert lib.tgvkv_abi_version() == bd.ABI_VERSION == 8
+    assert lib.tgvkv_abi_version() == bd.ABI_VERSION == 9
     for st in (0, -1, -2, -3, -4, -5):
         assert lib.tgvkv_status_string(st)
     assert lib.tgvkv_status_string(7) == b"unknown status"
@@ -303,6 +304,18 @@ def test_empty_batch_is_a_no_op(lib):
 def test_binding_fails_loudly_without_library(tmp_path):
     with pytest.raises(RuntimeError):
         bd.load_library(str(tmp_path / "missing.so"))
+
+
+def test_binding_refuses_a_library_without_its_options(tmp_path):
+    """ABI 8 knows no SCORE_ONE_ORDER and refuses every call of EvictionBuffers.evict: such a library does not load."""
+    src = tmp_path / "old.c"
+    both = bd.EXPORTS + bd.CEILING_EXPORTS
+    src.write_text("".join(f"long {n}(void) {{ return {8 if n == 'tgvkv_abi_version' else -1}; }}\n" for n in both))
+    so = tmp_path / "libold.so"
+    r = subprocess.run(["gcc", "-shared", "-fPIC", "-o", str(so), str(src)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr
+    with pytest.raises(RuntimeError, match="ABI 8"):
+        bd.load_library(str(so))
 
 
 @pytest.mark.skipif(_gpu(), reason="fake pointers are used only where no GPU exists")
