@@ -127,7 +127,7 @@ ScoreWs score_workspace(const Shape& s, const RowPlan& rp, void* base) {
     ScoreWs w;
     char* b = static_cast<char*>(base);
     w.vm = reinterpret_cast<float*>(b ? b + off : nullptr);  // [vision splits][B*L*H][N_q] row masses
-    off = align_up(off + sizeof(float) * bl * s.H * s.Nq * (size_t)tgvkv::vision_splits(s, rp));
+    off = align_up(off + sizeof(float) * bl * s.H * s.Nq * (size_t)tgvkv::vision_splits(s, rp, true));
     w.colsum = reinterpret_cast<float*>(b ? b + off : nullptr);
     off = align_up(off + sizeof(float) * bl * s.H * s.Nt);
     w.vmh = reinterpret_cast<float*>(b ? b + off : nullptr);

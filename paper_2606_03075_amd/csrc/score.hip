@@ -27,6 +27,7 @@
 // These kernels serve phase-by-phase calls (and the vision pass restricted to
 // layers whose budget reaches past the text).
 #include <algorithm>
+#include <climits>
 #include <map>
 #include <mutex>
 #include <tuple>
@@ -849,25 +850,42 @@ hipError_t launch_score_fin(const Shape& s, const float* ws_colsum, const float*
     return hipGetLastError();
 }
 
-int vision_splits(const Shape& s, const RowPlan& rp) {
-    // With few (unit, row group) workgroups the vision keys are split over several.  Below one round
-    // of resident workgroups (3 per CU up to four slots, else 2) the split fills one round, each
-    // share at least 2 key tiles: one video (112 units) in 4 shares 116 us against 125 us in 8
-    // (1.75 rounds); one layer of 128 units 32 -> 24.5 us.  Up to 2048 workgroups two rounds: at the
+// Workgroups of the vision sweep that fill a CU: 3, and 2 of the kernels whose registers allow no more, the plain
+// sweep of six slots at head_dim 128 and the mass-collecting one, which keeps a sum per row as well, from three
+// slots on (five at head_dim 64).  The small kernels fit more often, which measured no better (384 units
+// of 5 key tiles 17 us in 2 shares, 20 in 5).
+int vision_workgroups_per_cu(const Shape& s, const RowPlan& rp, bool mass) {
+    const int narrow = mass ? (s.D == 128 ? 3 : 5) : s.D == 128 ? 6 : 7;  // row slots from which 2
+    return rp.nslot >= narrow ? 2 : 3;
+}
+
+int vision_splits(const Shape& s, const RowPlan& rp, bool mass) {
+    // With few (unit, row group) workgroups the vision keys are split over several.  Up to 384, into the number
+    // of shares, each of 2 key tiles or more, whose rounds of resident workgroups take least, a round
+    // being the share's tiles and about two more to start and end it: one video (112 units) in 4 shares 116 us
+    // against 125 us in 8 (1.75 rounds); one layer of 128 units 32 -> 24.5 us.  The count of residents matters: with 3
+    // instead of 2 per CU, 128 units of 12 row blocks with given normalisers and 8192 vision keys took 123 us in 6
+    // shares, 99 in 4; with 2 instead of 3, 192 units of 20 blocks 182 us in 2, 154 in 4.  Up to
+    // 2048 workgroups two rounds: at the
     // Qwen2-VL shape (896 units, 2 workgroups per CU) two splits balance the last round (805 -> 740
     // us); at 4096 units a split only adds prologues.  The mass-collecting variant writes one row-mass
     // partial per share, which the reduction adds.
     const long long units = (long long)s.B * s.L * s.Hkv * rp.rowgroups;
     if (units <= 0) return 1;
-    const long long round = 256 * (rp.nslot <= 4 ? 3 : 2);
+    if (units > 384) return (int)std::min<long long>(std::max<long long>(2048 / units, 1), 4);
+    const long long round = 256LL * vision_workgroups_per_cu(s, rp, mass);
     const int tiles = (s.Nv + kTile - 1) / kTile;
-    if (units * 2 <= round) {
-        const int n = (int)std::max<long long>(
-            std::min<long long>(std::min<long long>(round / units, tiles / 2), kMaxShares), 1);
-        const int per = (tiles + n - 1) / n;  // tiles per share; no share is empty
-        return per > 0 ? (tiles + per - 1) / per : 1;
+    int best = 1;
+    long long least = LLONG_MAX;
+    for (int n = 1; n <= std::min(tiles / 2, kMaxShares); ++n) {
+        const int per = (tiles + n - 1) / n, shares = (tiles + per - 1) / per;  // no share is empty
+        const long long t = (units * shares + round - 1) / round * (per + 2);
+        if (t < least) {
+            least = t;
+            best = shares;
+        }
     }
-    return (int)std::min<long long>(std::max<long long>(2048 / units, 1), 4);
+    return best;
 }
 
 hipError_t launch_score_vision(const Shape& s, const RowPlan& rp, const uint16_t* q_text, const uint16_t* k,
@@ -875,7 +893,7 @@ hipError_t launch_score_vision(const Shape& s, const RowPlan& rp, const uint16_t
                                int32_t vis_threshold, float* ws_part, float* ws_vm, hipStream_t st) {
     const bool mass = ws_vm != nullptr;
     const long long units = (long long)s.B * s.L * s.Hkv * rp.rowgroups;
-    const int vsplit = vision_splits(s, rp);
+    const int vsplit = vision_splits(s, rp, mass);
     const long long nsh = units * vsplit;
     if (nsh == 0 || s.Nv == 0) return hipSuccess;
     // a unit's scores are kept in LDS and written once at the end when they fit (no global
@@ -939,7 +957,7 @@ hipError_t launch_score_vis_reduce(const Shape& s, const RowPlan& rp, const floa
     // With no question rows there are no partials (rowgroups == 0) and every score is zero.
     dim3 grid((unsigned)(nx + (int)mass), (unsigned)ny);
     hipLaunchKernelGGL(score_vis_reduce_kernel, grid, dim3(kThreads), 0, st, s, rp.rowgroups, ws_part, budgets,
-                       vis_threshold, s_vis, nx, ws_vm, tv_mass, vision_splits(s, rp));
+                       vis_threshold, s_vis, nx, ws_vm, tv_mass, vision_splits(s, rp, true));
     return hipGetLastError();
 }
 

@@ -50,7 +50,7 @@ hipError_t launch_score_vision(const Shape& s, const RowPlan& rp, const uint16_t
                                hipStream_t st);
 // Shares of the vision keys a unit's vision sweep is split over (the mass-collecting sweep
 // writes one row-mass partial per share).
-int vision_splits(const Shape& s, const RowPlan& rp);
+int vision_splits(const Shape& s, const RowPlan& rp, bool mass);
 // ws_vm non-null: the sweep's row masses, from which this also forms tv_mass.
 hipError_t launch_score_vis_reduce(const Shape& s, const RowPlan& rp, const float* ws_part,
                                    const int32_t* budgets, int32_t vis_threshold, float* s_vis,

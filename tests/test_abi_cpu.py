@@ -82,6 +82,16 @@ def test_long_decode_units_can_be_split(lib, units, splits):
     assert need <= 9 << 20
 
 
+@pytest.mark.parametrize("layers,n_vis,shares", [(32, 8192, 2), (32, 100, 1), (40, 8192, 3), (48, 600, 1), (64, 8192, 4)])
+def test_vision_shares_fill_rounds_of_the_mass_sweep(lib, layers, n_vis, shares):
+    """A CU holds two workgroups of the mass-collecting vision sweep at 12 row blocks, not three: shares are counted for
+    that (the workspace has a plane of row masses per share)."""
+    p = P(layers=layers, heads_q=32, heads_kv=8, n_sys=35, n_vis=n_vis, n_qst=40)
+    rest = [layers * 32 * (35 + 40), layers * 32, layers * 8 * n_vis]  # column sums, head masses, vision partials
+    up = lambda floats: (4 * floats + 255) // 256 * 256
+    assert bd.workspace_size(p, None, bd.CALL_SCORE) == up(layers * 32 * 40 * shares) + sum(map(up, rest))
+
+
 @pytest.mark.skipif(_gpu(), reason="fake pointers are used only where no GPU exists")
 def test_validation_before_any_launch(lib):
     fake = ctypes.c_void_p(0x10000)
