@@ -215,8 +215,8 @@ __device__ __forceinline__ void load_qrows(const Shape& s, const uint16_t* q_tex
 // per question row a reference max m (base-2 units, within 8 of the row's largest
 // logit), the sum of exp2(z - m) over visible keys and the same sum over vision
 // keys, so that m + log2(sum) is the row's normaliser.  On return the key-part-0
-// waves hold, in lanes 0..15, the merged statistics of their rows (with key_parts
-// each wave holds its own key part's); the workgroup is synced.
+// waves hold, in lanes 0..15, the merged statistics of their rows (of one share of a
+// unit's keys: each wave its own key part's); the workgroup is synced.
 // SHARES: every share_tiles tiles (an even number) start afresh, and the shares' statistics are
 // added in share order: the same bits as the sweeps of the shares one by one, merged so,
 // but with the tile pipeline running on.
@@ -224,7 +224,7 @@ template <int D, int NSLOT, int KS, bool SHARES = false>
 __device__ void stats_sweep(const Shape& s, const uint16_t* kbase, int kbeg, int kend,
                             const bf16x8 (&qf)[NSLOT][Geo<D>::KSTEPS], const int (&qrow)[NSLOT],
                             char (*tiles)[Geo<D>::TILE_BYTES], float (&m)[NSLOT], float (&lsum)[NSLOT],
-                            float (&vsum)[NSLOT], int share_tiles = 0, bool key_parts = false) {
+                            float (&vsum)[NSLOT], int share_tiles = 0, bool share = false) {
     using GG = Geo<D>;
     constexpr int RSETS = 4 / KS;
     constexpr int KBW = 4 / KS;
@@ -344,11 +344,23 @@ __device__ void stats_sweep(const Shape& s, const uint16_t* kbase, int kbeg, int
             }
         }
     };
+    // the same for a share, by row swaps on the VALU: it comes every few tiles (with merge_quarters' LDS shuffles
+    // four slots took a tenth longer at head_dim 64)
+    auto share_quarters = [&]() {
+#pragma unroll
+        for (int sl = 0; sl < NSLOT; ++sl) {
+            const float mn = max_xor32(max_xor16(m[sl]));
+            const float sc = fast_exp2(m[sl] - (mn == kNegInf ? 0.f : mn));
+            lsum[sl] = sum_xor32(sum_xor16((tsum[sl] + vsum[sl]) * sc));
+            vsum[sl] = sum_xor32(sum_xor16(vsum[sl] * sc));
+            m[sl] = mn;
+        }
+    };
     // SHARES: the shares' statistics, added in share order
     float sm[SHARES ? NSLOT : 1], sl_[SHARES ? NSLOT : 1], sv[SHARES ? NSLOT : 1];
     int next = share_tiles - 1;  // the share's last tile
     auto end_share = [&]() {
-        merge_quarters();
+        share_quarters();
 #pragma unroll
         for (int sl = 0; sl < NSLOT; ++sl) {
             if (next == share_tiles - 1) {
@@ -379,10 +391,12 @@ __device__ void stats_sweep(const Shape& s, const uint16_t* kbase, int kbeg, int
             lsum[sl] = sl_[sl];
             vsum[sl] = sv[sl];
         }
+    } else if (share) {
+        share_quarters();
     } else {
         merge_quarters();
     }
-    if (KS > 1 && !key_parts) {
+    if (KS > 1 && !share) {
         // waves of other key parts hand their partials to the key-part-0 wave of their row set
         float* red = reinterpret_cast<float*>(tiles[0]);  // [wave][NSLOT][16][3]
         if (kp > 0 && lane < 16) {
