@@ -643,7 +643,8 @@ RowPlan plan_question_rows(const Shape& s, bool one_order) {
 // where units are few: one video of 28 layers has 112, whose statistics and text took 299 us against 123.
 //
 // Shares for a single sequence to fill one round of resident workgroups (4, 3, 3, 2 per CU at 1, 2, 3, 4 and more row
-// slots), of four key tiles or more, in rows of 12 key tiles or more (6 where four slots or more make
+// slots), of four key tiles or more (six where a workgroup loads more than 16 row blocks, or one of several
+// groups of them, first: 128 units of 8275 keys in that plan 168 us in shares of four, 152 of six), in rows of 12 key tiles or more (6 where four slots or more make
 // each tile long and units are few).  Statistics and text, microseconds, whole / in shares: one layer of 32
 // units of 64 question rows, 1599 keys 31.9 / 22.4; of 4085 keys 57 / 26; one layer of 8 units of 200 rows, 4085 keys
 // 115 / 28; of 4 units of 336 rows, 8275 keys 294 / 39.  A sweep of one or two slots is a stream of
@@ -651,7 +652,6 @@ RowPlan plan_question_rows(const Shape& s, bool one_order) {
 // more units the longer.  Three and four slots give up their fused text pass for the shares
 // (stats_text_eligible), which costs large batches up to a tenth (512 units of 200 rows, 1599 keys: 100 / 109), so they
 // have the same limit.
-constexpr int kMinShareTiles = 4;
 constexpr int kMaxShares = 32;
 constexpr int kLightUnits = 128;
 
@@ -662,7 +662,8 @@ int share_tiles(const Shape& s, const RowPlan& rp) {
     if (rp.rowgroups == 1 && rp.nslot <= 4 && units > kLightUnits) return tiles;
     if (rp.rowgroups == 1 && rp.nslot <= 2 && units > 5LL * tiles * rp.nslot) return tiles;
     const int per_cu = rp.nslot == 1 ? 4 : rp.nslot <= 3 ? 3 : 2;
-    const int n = (int)std::min<long long>(std::min<long long>(256 * per_cu / units, tiles / kMinShareTiles), kMaxShares);
+    const int least = rp.nslot >= 5 || rp.rowgroups > 1 ? 6 : 4;
+    const int n = (int)std::min<long long>(std::min<long long>(256 * per_cu / units, tiles / least), kMaxShares);
     if (n <= 1) return tiles;
     const int per = (tiles + n - 1) / n;  // the last share takes what remains
     return rp.nslot <= 2 ? (per + 1) / 2 * 2 : per;  // an even number with two tiles in flight (stats_sweep)
