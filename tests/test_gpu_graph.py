@@ -67,6 +67,51 @@ def test_decode_graph_replays(lib, heads_q, heads_kv):
     assert torch.equal(buf.out, eager[T - 1])
 
 
+def test_decode_graphs_share_a_workspace(lib):
+    """Two decode calls of different shapes on one workspace, in one graph and in turn with eager calls of both: each
+    call's marks lie where the other's partials do, and a replay brings its old call numbers again."""
+    import torch
+    log("graph decode, two shapes on one workspace")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(9)
+    calls = []
+    for segments, heads_q, heads_kv in ((5, 14, 2), (40, 4, 4)):
+        bud = np.random.default_rng(segments).integers(0, 3000, segments).astype(np.int32)
+        seg = np.concatenate([[0], np.cumsum(bud.astype(np.int64) + 2)])
+        p = bd.make_problem(1, segments, heads_q, heads_kv, 128, 4, 3000, 8)
+        rand = lambda *shape: torch.randn(*shape, generator=g, device="cuda", dtype=torch.bfloat16)
+        cache = [rand(int(seg[-1]) * heads_kv * 128) for _ in range(2)]
+        new = [rand(1, segments, h, 128) for h in (heads_q, heads_kv, heads_kv)]
+        calls.append((p, cache, torch.from_numpy(bud).cuda(), torch.from_numpy(seg).cuda(), new,
+                      torch.empty(1, segments, heads_q, 128, device="cuda")))
+    ws = torch.full((max(bd.workspace_size(c[0], None, bd.CALL_DECODE) for c in calls),), 255, dtype=torch.uint8,
+                    device="cuda")
+
+    def step(c):
+        p, cache, bud, seg, new, out = c
+        bd.tgvkv_decode_attn(p, None, *cache, bud, seg, 2, 1, *new, out, ws)
+    want = []
+    for c in calls:
+        ws.fill_(255)
+        step(c)
+        want.append(c[-1].clone())
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        for c in calls + calls[:1]:
+            step(c)
+    for rep in range(4):
+        for c in calls:
+            c[-1].fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(c[-1], w) for c, w in zip(calls, want)), rep
+        c = calls[rep % 2]
+        c[-1].fill_(float("nan"))
+        step(c)
+        torch.cuda.synchronize()
+        assert torch.equal(c[-1], want[rep % 2]), rep
+
+
 @pytest.mark.parametrize("schedule", ["two_step", "phases"])
 def test_eviction_graph_replays(lib, schedule):
     """The whole eviction pass (scores, budgets, vision scores where needed, selection,

@@ -1,6 +1,9 @@
 """Launch plans away from the benchmark's shapes: each test runs a plan at the sizes where it changes, against the oracle.
 
-Scores use gpu_util's tolerance (2e-3 relative; 32-bit sums are observed near 1e-6)."""
+Scores are held to 2e-5 of the 64-bit oracle: logits up to 20 in base 2, rounded in 32 bits, move an exponential by about
+2e-6, and the sums of positive terms, in partial sums of a few hundred terms, as much again.  One key left out or
+counted twice at the edge of a share or a ragged tile shows (test_ranges_cpu.py): it moves the normaliser of some row by
+more than that."""
 
 import numpy as np
 import pytest
@@ -22,6 +25,9 @@ def lib():
     return bd.load_library()
 
 
+SCORE_BOUND = 2e-5  # absolute for the normalisers (natural log), relative for the scores
+
+
 def check_scores(cfg, head_mode=0, phase_lists=((bd.SCORE_ALL,),)):
     """Scores of every (sequence, layer) against the oracle, for each way of asking for the phases."""
     import torch
@@ -40,33 +46,35 @@ def check_scores(cfg, head_mode=0, phase_lists=((bd.SCORE_ALL,),)):
         for b in range(cfg.batch):
             for l in range(cfg.layers):
                 r = ref[b][l]
-                assert_close_rel("lse", host(buf.lse[b, l]), r["lse"], atol=1e-4)
+                assert_close_rel("lse", host(buf.lse[b, l]), r["lse"], rtol=0.0, atol=SCORE_BOUND)
                 for n in ("s_txt", "w_txt", "tv_mass", "s_vis"):
-                    assert_close_rel(n, host(getattr(buf, n)[b, l]), r[n])
+                    assert_close_rel(n, host(getattr(buf, n)[b, l]), r[n], rtol=SCORE_BOUND)
 
 
 SPLIT_STATS = {
-    # 12 and 11 key tiles of one row slot per wave: the shortest split sweep and the longest whole one
+    # 12 and 11 key tiles of one row slot per wave: the shortest sweep in shares and the longest whole one
     "short_12_tiles": dict(heads_q=4, heads_kv=4, n_sys=5, n_vis=690, n_qst=50),
     "whole_11_tiles": dict(heads_q=4, heads_kv=4, n_sys=5, n_vis=650, n_qst=49),
-    # 21 row blocks, six slots: 6 key tiles, the last of a single key
-    "gqa7_6_tiles": dict(heads_q=14, heads_kv=2, n_sys=17, n_vis=256, n_qst=48),
+    # 21 row blocks, six slots: two shares, the last tile a single key
+    "gqa7_last_key": dict(heads_q=14, heads_kv=2, n_sys=17, n_vis=704, n_qst=48),
+    # two key parts: a last share of one tile, its last key alone in a 16-key block
+    "key_parts": dict(heads_q=2, heads_kv=2, n_sys=7, n_vis=800, n_qst=26),
     # shares that hold no vision key, or nothing but masked question keys for the early rows
     "question_shares": dict(heads_q=2, heads_kv=2, n_sys=130, n_vis=70, n_qst=700),
     "system_shares": dict(heads_q=2, heads_kv=2, n_sys=700, n_vis=70, n_qst=20),
-    # several row groups per unit, each split; the text pass per query head in chunks of key blocks
-    "row_groups": dict(heads_q=16, heads_kv=1, n_sys=40, n_vis=300, n_qst=160),
+    # several row groups per unit, each in shares; the text pass per query head in chunks of key blocks
+    "row_groups": dict(heads_q=16, heads_kv=1, n_sys=40, n_vis=900, n_qst=160),
     # text rows that do not fit the staged text pass
     "long_text_split": dict(heads_q=2, heads_kv=1, n_sys=10, n_vis=100, n_qst=4000, layers=1),
-    # the most shares, and head_dim 64 with no system text
-    "many_shares": dict(heads_q=3, heads_kv=1, n_sys=9, n_vis=6800, n_qst=33),
+    # many shares, and head_dim 64 with no system text
+    "many_shares": dict(heads_q=3, heads_kv=1, n_sys=9, n_vis=8300, n_qst=33),
     "d64": dict(heads_q=8, heads_kv=2, head_dim=64, n_sys=0, n_vis=900, n_qst=19),
 }
 
 
 @pytest.mark.parametrize("name", sorted(SPLIT_STATS))
 def test_split_statistics(lib, name):
-    """The statistics sweep with its keys split over workgroups, merged by the text pass (both phases in
+    """The statistics sweep in shares of the keys: with workgroups of their own, merged by the text pass (both phases in
     one call) and by the merge kernel (statistics alone, then text)."""
     log(f"split statistics {name}")
     cfg = custom_config(name=name, **dict(dict(batch=1, layers=2), **SPLIT_STATS[name]))
@@ -74,7 +82,7 @@ def test_split_statistics(lib, name):
 
 
 SPLIT_VISION = {
-    # 3-tile shares, the last one ragged; shares of a row plan with its own vision launch shape; two row groups
+    # shares of a few tiles, the last one ragged; shares of a row plan with its own vision launch shape; two row groups
     "mha": dict(heads_q=4, heads_kv=4, n_sys=5, n_vis=1201, n_qst=50),
     "three_blocks": dict(heads_q=4, heads_kv=4, n_sys=0, n_vis=449, n_qst=40),
     "below_a_share": dict(heads_q=4, heads_kv=4, n_sys=3, n_vis=190, n_qst=20),
