@@ -179,9 +179,9 @@ __global__ __launch_bounds__(kThreads) void score_stats_merge_kernel(Shape s, co
 template <int NSLOT, int KS>
 constexpr bool kQregsText = (NSLOT == 3 || NSLOT == 4) && KS == 1;
 
-// With three or four row slots the kernel is held to 168 registers, 3 waves per SIMD: it then spills
-// 96 bytes a lane, all outside the sweep's tile loops (at its phase changes and in the text
-// pass), and at the 13B stress shape it took 6.84 ms against 7.21-7.25 ms at 2 waves per SIMD.
+// With three or four row slots the kernel is held to 168 registers, 3 waves per SIMD: with text mode 2 it then spills
+// 16 or 96 bytes a lane, all outside the sweep's tile loops (at its phase changes and in the text pass),
+// and at the 13B stress shape (four slots) it took 6.84 ms against 7.21-7.25 ms at 2 waves per SIMD.
 // QREGS: a kernel of its own for text mode 2, without the other modes' code: their calls beside the
 // spills at 168 registers cost the 13B stress shape 5 %.
 // SHARES: the unit's keys are summed in shares of share_tiles tiles and the text pass's columns BY_ROW, to the
@@ -618,13 +618,14 @@ RowPlan plan_question_rows(const Shape& s, bool one_order) {
         rp.rowgroups = NB > 0 ? 1 : 0;
         return rp;
     }
-    // the fewest row groups of at most 4 waves x 6 slots (each group reads the unit's keys), the
-    // blocks dealt evenly over them, and no more slots per wave than that takes: an empty slot
-    // costs the statistics sweep as much as a full one.  Statistics (with the text pass where it is
-    // fused) and vision sweep, against slot counts of 2, 4 or 6 filled from the first group on:
+    // the fewest row groups of at most 4 waves x 6 slots (each group reads the unit's keys), all with the
+    // same slots per wave, no more than it takes: an empty slot costs the statistics sweep as much as
+    // a full one.  (The groups fill up in turn: 28 blocks run as 16 + 12.)  Statistics (with the text pass
+    // where it is fused) and vision sweep, against slot counts of 2, 4 or 6 filled from the first group on:
     // 12 blocks 3 slots 626 + 473 against 4 slots 793 + 449 us (80 units of 40 heads, 2215 keys);
-    // 20 blocks 5 slots 400 + 335 against 6 slots 426 + 374; 28 blocks 2 x 14 389 + 336 against
-    // 24 + 4 418 + 435; 21 blocks as 2 x 11 instead of one group: 955 + 944 against 841 + 794.
+    // 20 blocks 5 slots 400 + 335 against 6 slots 426 + 374; 28 blocks in two groups of 4 slots 389 + 336
+    // against 24 + 4 blocks 418 + 435; 21 blocks in two groups of 3 slots instead of one of 6: 955 + 944
+    // against 841 + 794.
     rp.rowgroups = (NB + 23) / 24;
     rp.ks = 1;
     if (one_order) {
@@ -862,7 +863,7 @@ int vision_workgroups_per_cu(const Shape& s, const RowPlan& rp, bool mass) {
 
 int vision_splits(const Shape& s, const RowPlan& rp, bool mass) {
     // With few (unit, row group) workgroups the vision keys are split over several.  Up to 384, into the number
-    // of shares, each of 2 key tiles or more, whose rounds of resident workgroups take least, a round
+    // of shares, each of 2 key tiles or more but the last, whose rounds of resident workgroups take least, a round
     // being the share's tiles and about two more to start and end it: one video (112 units) in 4 shares 116 us
     // against 125 us in 8 (1.75 rounds); one layer of 128 units 32 -> 24.5 us.  The count of residents matters: with 3
     // instead of 2 per CU, 128 units of 12 row blocks with given normalisers and 8192 vision keys took 123 us in 6
