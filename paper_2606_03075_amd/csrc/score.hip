@@ -645,10 +645,11 @@ RowPlan plan_question_rows(const Shape& s, bool one_order) {
 //
 // Shares for a single sequence to fill one round of resident workgroups (4, 3, 3, 2 per CU at 1, 2, 3, 4 and more row
 // slots), of four key tiles or more (six where a workgroup loads more than 16 row blocks, or one of several
-// groups of them, first: 128 units of 8275 keys in that plan 168 us in shares of four, 152 of six), in rows of 12 key tiles or more (6 where four slots or more make
-// each tile long and units are few).  Statistics and text, microseconds, whole / in shares: one layer of 32
-// units of 64 question rows, 1599 keys 31.9 / 22.4; of 4085 keys 57 / 26; one layer of 8 units of 200 rows, 4085 keys
-// 115 / 28; of 4 units of 336 rows, 8275 keys 294 / 39.  A sweep of one or two slots is a stream of
+// groups of them, first: 128 units of 8275 keys in that plan 168 us in shares of four, 152 of six), in rows
+// of 12 key tiles or more (6 where three slots or more make each tile long and units are few).  Statistics
+// and text, microseconds, whole / in shares: one layer of 32 units of 64 question rows, 1599 keys
+// 31.9 / 22.4; of 4085 keys 57 / 26; one layer of 8 units of 200 rows, 4085 keys 115 / 28; of 4 units of
+// 336 rows, 8275 keys 294 / 39.  A sweep of one or two slots is a stream of
 // keys, and half the CUs already draw much of the bandwidth: only sequences of up to 128 units, and the
 // more units the longer.  Three and four slots give up their fused text pass for the shares
 // (stats_text_eligible), which costs large batches up to a tenth (512 units of 200 rows, 1599 keys: 100 / 109), so they
