@@ -70,15 +70,46 @@ struct Splits {
     int span;                   // units per 256 workgroups
 };
 
-// Splits of a unit of `len` rows (len is known on the device only).  The TVB budgets of one call differ by
-// an order of magnitude, and without more splits for its longest units these set the time: 160 units of
-// 400 to 4000 rows, mean 1500, one query head: 42.1 us with one workgroup each, 30.1 so; 132 units of up to
-// 10000 rows, seven query heads, 137 against 59.  Below kWholeRows a split costs more than it evens out
-// (160 units of 700 rows: 13.8 us whole, 16.6 in two).
+// Splits of a unit of `len` rows (len is known on the device only); called by whole waves, with the same
+// arguments in every workgroup of the unit.
+//
+// The TVB budgets of one call differ by an order of magnitude, and without more splits for its longest units
+// these set the time: 160 units of 400 to 4000 rows, mean 1500, one query head: 42.1 us with one workgroup each,
+// 30.1 in splits; 132 units of up to 10000 rows, seven query heads, 137 against 59.  A call of even lengths
+// gains nothing: 168 units of 1130 rows take 19.5 us whole, 23.2 in three splits each; 400 units of 2000 rows 67
+// against 73.  So the units are split only where the longest keeps its CU well beyond the call's mean load of a
+// CU (with more units than CUs, the longest and one of mean length): by half and 700 rows, the extra
+// partials' cost.  The line lies between 132 units of 2000 rows (28.6 us whole, 33.3 split) and of 4000 rows (52.5
+// against 48.4), and 168 units of 810 to 1620 rows (22.9 against 27.9) and of 2870 to 5740 rows (66 against 58.6).
+// Reading the lengths costs a call of whole units over kWholeRows 1 to 2 us (the 19.5 us above now 21.0).  A call
+// of no unit over kWholeRows is not worth the look (160 units of 700 rows: 13.8 us whole, 16.6 in two).
 constexpr int kWholeRows = 1024;
-__device__ __forceinline__ int unit_splits(int len, const Splits& sp) {
-    const int n = len <= kWholeRows ? 1 : (len + sp.rows - 1) / sp.rows;
-    return min(max(sp.base, n), sp.most);
+__device__ __forceinline__ int unit_splits(const Splits& sp, const Shape& s, int len, const int32_t* budgets,
+                                           const int32_t* steps, int step, int reserve) {
+    if (len <= kWholeRows || sp.base == sp.most) return sp.base;
+    const int segments = s.B * s.L;
+    float longest = 0.f, rows = 0.f;  // of the segments that decode
+    for (int i0 = threadIdx.x & 63; i0 < segments; i0 += 256) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int i = min(i0 + 64 * u, segments - 1);
+            const int st = steps != nullptr ? steps[i / s.L] : step;
+            const float rows_i = (float)(budgets[i] + st + 1);
+            if (i0 + 64 * u < segments && st >= 0 && st < reserve) {
+                longest = fmaxf(longest, rows_i);
+                rows += rows_i;
+            }
+        }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        longest = fmaxf(longest, __shfl_xor(longest, o));
+        rows += __shfl_xor(rows, o);
+    }
+    float load = longest / sp.base;
+    if (segments * s.Hkv > kCUs) load += rows / segments;
+    if (load <= 1.5f * (rows * s.Hkv / kCUs) + 700.f) return sp.base;
+    return min(max(sp.base, (len + sp.rows - 1) / sp.rows), sp.most);
 }
 
 // The (unit, split) of a workgroup; false for none.  Each 256 workgroups, one per CU, hold every split of
@@ -204,7 +235,7 @@ __global__ __launch_bounds__(kThreads) void decode_kernel(Shape s, Rows rows, ui
     if (st < 0 || st >= reserve) return;  // uniform over the workgroup, before any barrier
     const int bsz = budgets[bl];
     const int len = bsz + st + 1;
-    const int nsplit = SPLIT ? unit_splits(len, sp) : 1;
+    const int nsplit = SPLIT ? unit_splits(sp, s, len, budgets, steps, step, reserve) : 1;
     if (SPLIT && split >= nsplit) return;  // uniform, before any barrier
     rows.init(s, bl, kvh, bsz, len, lds_pages);
     __syncthreads();
@@ -433,7 +464,7 @@ __global__ __launch_bounds__(kThreads) void decode_mfma_kernel(Shape s, Rows row
     if (st < 0 || st >= reserve) return;  // uniform over the workgroup, before any barrier
     const int bsz = budgets[bl];
     const int len = bsz + st + 1;
-    const int nsplit = SPLIT ? unit_splits(len, sp) : 1;
+    const int nsplit = SPLIT ? unit_splits(sp, s, len, budgets, steps, step, reserve) : 1;
     if (SPLIT && split >= nsplit) return;  // uniform, before any barrier
     rows.init(s, bl, kvh, bsz, len, lds_pages);
     __syncthreads();

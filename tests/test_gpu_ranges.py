@@ -308,6 +308,41 @@ def test_split_decode(lib, segments, heads_q, heads_kv, head_dim):
         decode_steps(bud, heads_q, heads_kv, head_dim, 3, 3, fill)
 
 
+@pytest.mark.parametrize("heads_q,heads_kv,head_dim", [(4, 4, 128), (28, 4, 128), (8, 4, 64)])
+@pytest.mark.parametrize("segments,rows", [(33, 1500), (42, 2000), (100, 1100), (128, 1300)])
+def test_decode_units_of_even_lengths_stay_whole(lib, segments, rows, heads_q, heads_kv, head_dim):
+    """129 to 512 units of equal lengths are not split (that costs up to a fifth): the same bits as in a call of more
+    than 512 units, which has no splits; one unit of eight times the length and more, and they are."""
+    import torch
+    log(f"even decode {segments} segments of {rows} rows {heads_q}/{heads_kv} d{head_dim}")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(segments)
+    many, reserve, last = 130, 2, 9000
+    p = lambda n: bd.make_problem(1, n, heads_q, heads_kv, head_dim, 4, last, 8)
+    total = heads_kv * head_dim * (many * (rows + reserve) + last)
+    cache = [torch.randn(total, generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(2)]
+    q, kn, vn = (torch.randn(1, many, h, head_dim, generator=g, device="cuda", dtype=torch.bfloat16)
+                 for h in (heads_q, heads_kv, heads_kv))
+
+    def decode(n, longest=0):
+        bud = np.full(n, rows, np.int32)
+        if longest:
+            bud[-1] = longest
+        seg = np.concatenate([[0], np.cumsum(bud.astype(np.int64) + reserve)])
+        out = torch.full((1, n, heads_q, head_dim), float("nan"), device="cuda")
+        ws = torch.zeros(max(bd.workspace_size(p(n), None, bd.CALL_DECODE), 1), device="cuda", dtype=torch.uint8)
+        part = [t[:, :n].contiguous() for t in (q, kn, vn)]
+        bd.tgvkv_decode_attn(p(n), None, *cache, torch.from_numpy(bud).cuda(), torch.from_numpy(seg).cuda(), reserve,
+                             0, *part, out, ws)
+        return out
+
+    whole = decode(many)
+    assert torch.equal(decode(segments), whole[:, :segments])
+    split = decode(segments, last)[:, :segments - 1]
+    assert (split - whole[:, :segments - 1]).abs().max().item() <= 2e-4  # each within 1e-4 of 64 bits
+    assert not torch.equal(split, whole[:, :segments - 1])
+
+
 @pytest.mark.parametrize("heads_q,heads_kv,head_dim", [(4, 4, 128), (4, 2, 64), (28, 4, 128), (32, 4, 64)])
 @pytest.mark.parametrize("segments", [5, 33, 56, 75, 128])
 def test_split_decode_of_uneven_lengths(lib, segments, heads_q, heads_kv, head_dim):
