@@ -343,6 +343,57 @@ def test_decode_units_of_even_lengths_stay_whole(lib, segments, rows, heads_q, h
     assert not torch.equal(split, whole[:, :segments - 1])
 
 
+@pytest.mark.parametrize("heads_q,heads_kv,layers", [(2, 1, 11), (8, 1, 11), (8, 4, 3)])
+def test_idle_sequences_do_not_split_the_others(lib, heads_q, heads_kv, layers):
+    """Paged decode, each sequence at its own step: a long one that does not decode leaves the others whole, the same
+    bits as without it; decoding, it has them split, each output within 1e-4 of 64 bits."""
+    import torch
+    log(f"idle long sequence {heads_q}/{heads_kv} {layers} layers")
+    g = torch.Generator(device="cuda")
+    g.manual_seed(layers)
+    batch, rows, last, reserve, page, D = 24 if heads_kv == 1 else 12, 1100, 8000, 4, 64, 128
+    n = batch * layers
+    width = -(-(last + reserve) // page)
+    p = bd.make_problem(batch, layers, heads_q, heads_kv, D, 1, 0, 0)
+    short = -(-(rows + reserve) // page)  # pages of a short segment; the last sequence's have `width` each
+    pages = (n - layers) * short + layers * width
+    table = np.full((n, width), -1, np.int32)
+    ids = np.random.default_rng(layers).permutation(pages).astype(np.int32)
+    for s in range(n):
+        first = min(s, n - layers) * short + max(s - (n - layers), 0) * width
+        table[s, :short if s < n - layers else width] = ids[first:first + (short if s < n - layers else width)]
+    k, v = (torch.randn(pages, heads_kv, page, D, generator=g, device="cuda", dtype=torch.bfloat16) for _ in range(2))
+    q, kn, vn = (torch.randn(batch, layers, h, D, generator=g, device="cuda", dtype=torch.bfloat16)
+                 for h in (heads_q, heads_kv, heads_kv))
+    steps = np.arange(batch, dtype=np.int32) % reserve
+
+    def decode(longest, idle):
+        bud = np.full(n, rows, np.int32)
+        bud[n - layers:] = longest
+        st = steps.copy()
+        if idle:
+            st[-1] = -1
+        out = torch.full((batch, layers, heads_q, D), float("nan"), device="cuda")
+        ws = torch.zeros(max(bd.workspace_size(p, None, bd.CALL_DECODE), 1), device="cuda", dtype=torch.uint8)
+        kc, vc = k.clone(), v.clone()
+        bd.tgvkv_decode_attn_paged(p, None, kc, vc, page, torch.from_numpy(table).cuda(), torch.from_numpy(bud).cuda(),
+                                   reserve, torch.from_numpy(st).cuda(), q, kn, vn, out, ws)
+        for b in range(batch - 1 if idle else batch):
+            for l in range(layers):
+                m = int(bud[b * layers + l]) + int(st[b]) + 1
+                at = torch.from_numpy(table[b * layers + l, :-(-m // page)].astype(np.int64)).cuda()
+                K, V = (c[at].transpose(0, 1).reshape(heads_kv, -1, D)[:, :m].double() for c in (kc, vc))
+                assert torch.equal(K[:, -1], kn[b, l].double())
+                z = torch.matmul(q[b, l].double().view(heads_kv, -1, D), K.transpose(1, 2).contiguous())
+                want = torch.matmul(torch.softmax(z / D ** 0.5, -1), V).view(heads_q, D)
+                assert (out[b, l].double() - want).abs().max().item() <= 1e-4, (longest, idle, b, l)
+        return out[:-1]
+
+    even = decode(rows, False)
+    assert torch.equal(decode(last, True), even)
+    assert not torch.equal(decode(last, False), even)
+
+
 @pytest.mark.parametrize("heads_q,heads_kv,head_dim", [(4, 4, 128), (4, 2, 64), (28, 4, 128), (32, 4, 64)])
 @pytest.mark.parametrize("segments", [5, 33, 56, 75, 128])
 def test_split_decode_of_uneven_lengths(lib, segments, heads_q, heads_kv, head_dim):
